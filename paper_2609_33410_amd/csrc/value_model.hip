@@ -2,12 +2,21 @@
 // dial": cut keys are modelled by the request's running mean, which needs no
 // fit).
 //
-// value_mean_kernel: one workgroup of 16 wave64s per (kv sequence, kv head) of
-// a per-request view.  Wave w adds the value rows of keys w, w + 16, ...; lane l
-// owns channels [l D/64, (l + 1) D/64), so a key row is one coalesced read.  The
-// waves' sums are added in wave order through LDS and divided by the length.
-// Bound by HBM bandwidth over the request's values (a prompt-time call).
-//
+// value_mean_kernel: one workgroup of 16 wave64s per (kv sequence, kv head,
+// 32-channel segment) of a per-request view.  Four lanes hold a key's segment (64
+// bytes), so a wave-wide load takes the segment of one 16-key chunk; wave w
+// adds chunks w, w + 16, ..., eight loads in flight.  The lanes' sums are
+// added by a butterfly, the waves' in wave order through LDS, and divided by
+// the length.  Bound by HBM bandwidth over the request's values (a prompt-time
+// call).  Splitting the channels (not the keys) needs no partial sums between
+// workgroups, hence no workspace, and gives num_seqs * hkv * D/32 workgroups:
+// one per (sequence, head) alone left most of the chip idle.  The segments of
+// a row lie 64 bytes apart in one 128-byte line, so their workgroups keep the
+// same index mod 8 (one XCD, one L2) when num_seqs * hkv is a multiple of 8.
+// 4 x 8192 keys, 8 kv heads, D = 128 (67 MB), right after the append that
+// wrote them: 477 us with one workgroup per (sequence, head), 29.5 us now (64-
+// or 32-channel segments, 8 or 16 loads in flight and either cache policy are
+// within 0.5 us of each other; the rest is the append's dirty lines).
 // value_mean_append_kernel: one wave64 per (token, kv head): the running
 // update mu += (v - mu) / (pos + 1) for a token appended at position pos.
 //
@@ -40,41 +49,89 @@ namespace {
 constexpr int kMeanWaves = 16;
 constexpr int kMeanThreads = 64 * kMeanWaves;
 
-template <int D>
+constexpr int kMeanSeg = 32;      // channels per workgroup
+constexpr int kMeanInFlight = 8;  // chunk loads in flight per lane
+
+// WIDE: v is 16-byte aligned (one 16-byte load per lane); else eight 2-byte
+// loads.
+template <int D, bool WIDE>
 __global__ __launch_bounds__(kMeanThreads) void value_mean_kernel(const MeanArgs a) {
-  constexpr int CPL = D / 64;  // channels per lane
   const ScanGeometry& g = a.geo;
-  const int seq = blockIdx.x / g.hkv;
-  const int kvh = blockIdx.x % g.hkv;
+  const int items = g.num_seqs * g.hkv;
+  const int item = blockIdx.x % items;
+  const int seg = blockIdx.x / items;
+  const int seq = item / g.hkv;
+  const int kvh = item % g.hkv;
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = clamp_len(ld_uniform(g.seq_lens, seq), view_capacity(g));
-  float sum[CPL];
+  const int nchunks = (n + kChunk - 1) / kChunk;
+  const int m = nchunks > wave ? (nchunks - wave + kMeanWaves - 1) / kMeanWaves : 0;
+  const uint32_t lane_off = (lane >> 2) * (2 * D) + seg * (2 * kMeanSeg) + 16 * (lane & 3);
+  float sum[8];
 #pragma unroll
-  for (int c = 0; c < CPL; ++c) sum[c] = 0.0f;
-  for (int j = wave; j < n; j += kMeanWaves) {
-    size_t row;
-    bool ok = true;
-    if (g.page_size > 0) {
-      const int phys = g.block_table[static_cast<size_t>(seq) * g.max_pages + j / g.page_size];
-      ok = phys >= 0 && phys < g.num_pages;
-      row = (static_cast<size_t>(ok ? phys : 0) * g.hkv + kvh) * g.page_size + j % g.page_size;
-    } else {
-      row = (static_cast<size_t>(seq) * g.hkv + kvh) * g.max_seq_len + j;
+  for (int e = 0; e < 8; ++e) sum[e] = 0.0f;
+  int pt = 0;  // block-table entries of 64 of the wave's chunks, one per lane
+  for (int k0 = 0; k0 < m; k0 += kMeanInFlight) {
+    if (k0 % 64 == 0 && g.page_size > 0) {
+      const int c = wave + (k0 + lane) * kMeanWaves;
+      pt = c < nchunks ? g.block_table[static_cast<size_t>(seq) * g.max_pages +
+                                       (c * kChunk) / g.page_size]
+                       : 0;
     }
-    if (!ok) continue;  // uniform: the page id is outside the pool
-    const uint16_t* v = g.v + row * D + CPL * lane;
+    u32x4 v[kMeanInFlight];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) sum[c] += bf16_lo(v[c]);
+    for (int u = 0; u < kMeanInFlight; ++u) {
+      const int k = k0 + u;
+      const int c = wave + k * kMeanWaves;
+      size_t row = 0;
+      int keys = k < m ? min(kChunk, n - c * kChunk) : 0;
+      if (g.page_size > 0) {
+        const int phys = __builtin_amdgcn_readlane(pt, k & 63);
+        if (phys >= 0 && phys < g.num_pages)
+          row = (static_cast<size_t>(phys) * g.hkv + kvh) * g.page_size + (c * kChunk) % g.page_size;
+        else
+          keys = 0;  // a page id outside the pool adds nothing
+      } else if (k < m) {
+        row = (static_cast<size_t>(seq) * g.hkv + kvh) * g.max_seq_len + c * kChunk;
+      }
+      if constexpr (WIDE) {
+        v[u] = buf_load(make_rsrc(g.v + row * D, static_cast<uint32_t>(keys) * 2 * D), lane_off);
+      } else {
+        uint32_t w[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          w[e] = (lane >> 2) < keys ? (g.v + row * D)[lane_off / 2 + e] : 0u;
+        v[u] = u32x4{w[0] | (w[1] << 16), w[2] | (w[3] << 16), w[4] | (w[5] << 16),
+                     w[6] | (w[7] << 16)};
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kMeanInFlight; ++u) {
+      sum[0] += bf16_lo(v[u].x);
+      sum[1] += bf16_hi(v[u].x);
+      sum[2] += bf16_lo(v[u].y);
+      sum[3] += bf16_hi(v[u].y);
+      sum[4] += bf16_lo(v[u].z);
+      sum[5] += bf16_hi(v[u].z);
+      sum[6] += bf16_lo(v[u].w);
+      sum[7] += bf16_hi(v[u].w);
+    }
   }
-  __shared__ float red[kMeanWaves][D];
 #pragma unroll
-  for (int c = 0; c < CPL; ++c) red[wave][CPL * lane + c] = sum[c];
+  for (int off = 4; off < 64; off <<= 1)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sum[e] += __shfl_xor(sum[e], off, 64);
+  __shared__ float red[kMeanWaves][kMeanSeg];
+  if (lane < 4)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[wave][8 * lane + e] = sum[e];
   __syncthreads();
-  for (int d = threadIdx.x; d < D; d += kMeanThreads) {
+  if (threadIdx.x < kMeanSeg) {
     float t = 0.0f;
-    for (int w = 0; w < kMeanWaves; ++w) t += red[w][d];
-    a.mean[(static_cast<size_t>(seq) * g.hkv + kvh) * D + d] = n > 0 ? t / static_cast<float>(n) : 0.0f;
+    for (int w = 0; w < kMeanWaves; ++w) t += red[w][threadIdx.x];
+    a.mean[static_cast<size_t>(item) * D + seg * kMeanSeg + threadIdx.x] =
+        n > 0 ? t / static_cast<float>(n) : 0.0f;
   }
 }
 
@@ -268,6 +325,12 @@ hipError_t launch_bm_d(const BlockModelArgs& a, int rb, unsigned blocks, hipStre
   }
 }
 
+template <int D, bool WIDE>
+hipError_t launch_mean(const MeanArgs& a, unsigned blocks, hipStream_t stream) {
+  hipLaunchKernelGGL((value_mean_kernel<D, WIDE>), dim3(blocks), dim3(kMeanThreads), 0, stream, a);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 int block_model_rows(int rows_per_seq) {
@@ -313,17 +376,15 @@ hipError_t launch_block_model(const BlockModelArgs& a, int head_dim, hipStream_t
 }
 
 hipError_t launch_value_mean(const MeanArgs& a, int head_dim, hipStream_t stream) {
-  const long long blocks = static_cast<long long>(a.geo.num_seqs) * a.geo.hkv;
+  if (head_dim != 64 && head_dim != 128) return hipErrorInvalidValue;
+  const long long blocks =
+      static_cast<long long>(a.geo.num_seqs) * a.geo.hkv * (head_dim / kMeanSeg);
   if (blocks == 0) return hipSuccess;
+  const bool wide = (reinterpret_cast<uintptr_t>(a.geo.v) & 15u) == 0;
+  const unsigned grid = static_cast<unsigned>(blocks);
   if (head_dim == 128)
-    hipLaunchKernelGGL(value_mean_kernel<128>, dim3(static_cast<unsigned>(blocks)),
-                       dim3(kMeanThreads), 0, stream, a);
-  else if (head_dim == 64)
-    hipLaunchKernelGGL(value_mean_kernel<64>, dim3(static_cast<unsigned>(blocks)),
-                       dim3(kMeanThreads), 0, stream, a);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+    return wide ? launch_mean<128, true>(a, grid, stream) : launch_mean<128, false>(a, grid, stream);
+  return wide ? launch_mean<64, true>(a, grid, stream) : launch_mean<64, false>(a, grid, stream);
 }
 
 hipError_t launch_value_mean_append(const MeanArgs& a, int head_dim, hipStream_t stream) {
