@@ -167,6 +167,7 @@ __device__ __forceinline__ void front_split_rows(const Q8EstimateArgs& qa8, int 
                                                  bool write_out) {
   const ScanGeometry& g = qa8.e.geo;
   const int lane = threadIdx.x & 63;
+  const int el = hadamard_lane(lane);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int G = g.group;
   for (int r = wave; r < G; r += NT / 64) {
@@ -174,7 +175,7 @@ __device__ __forceinline__ void front_split_rows(const Q8EstimateArgs& qa8, int 
     double x[D / 64];
 #pragma unroll
     for (int i = 0; i < D / 64; ++i)
-      x[i] = static_cast<double>(bf16_lo(qa8.q_src[row * D + 64 * i + lane]));
+      x[i] = static_cast<double>(bf16_lo(qa8.q_src[row * D + 64 * i + el]));
     hadamard_wave<D>(x, lane);
     const double f = wave_absmax_f64<D>(x) / 127.0;
 #pragma unroll
@@ -182,11 +183,11 @@ __device__ __forceinline__ void front_split_rows(const Q8EstimateArgs& qa8, int 
       int8_t ca, cb;
       split_value(x[i], f, &ca, &cb);
       if (write_out) {
-        qa8.qp_out[row * 2 * D + 64 * i + lane] = ca;
-        qa8.qp_out[row * 2 * D + D + 64 * i + lane] = cb;
+        qa8.qp_out[row * 2 * D + 64 * i + el] = ca;
+        qa8.qp_out[row * 2 * D + D + 64 * i + el] = cb;
       }
-      qs[r][64 * i + lane] = ca;
-      qs[r][D + 64 * i + lane] = cb;
+      qs[r][64 * i + el] = ca;
+      qs[r][D + 64 * i + el] = cb;
     }
     if (lane == 0) {
       const float eta = static_cast<float>(((kLog2eF64 * static_cast<double>(qa8.sm_scale)) * f) / D);

@@ -1,11 +1,15 @@
 """Prompt-time calls at the sizes where their work split can go wrong: the
 request means (chunk windows, partial chunks, odd pages, unaligned values) and
-the bulk append (tokens per workgroup, ragged remainders, skipped tokens)."""
+the bulk append (tokens per workgroup, ragged remainders, skipped tokens) and
+the writers of the 8-bit formats (rows per workgroup, rounding, alignment)."""
 
+import numpy as np
 import pytest
 import torch
 
 import paper_2609_33410_amd as F
+from oracle import q8_oracle as q8
+from workloads import host_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -121,3 +125,92 @@ def test_append_whole_prompts(d, hkv, n_tok, which):
             at = ok.nonzero()[:, 0].cuda()
             want[phys[ok].cuda(), :, (pos[ok] % page).cuda()] = rows[at]
         assert torch.equal(cache, want)
+
+
+def _shifted(t, wide):
+    """t itself, or a copy of it two bytes past a 16-byte boundary."""
+    if wide:
+        return t
+    raw = torch.empty(t.numel() * t.element_size() + 32, dtype=torch.uint8, device="cuda")
+    off = (-raw.data_ptr()) % 16 + 2
+    out = raw[off:off + t.numel() * t.element_size()].view(t.dtype).view(t.shape)
+    out.copy_(t)
+    assert out.data_ptr() % 16 == 2
+    return out
+
+
+def _write_all(fn, src, arrays, hkv, wide):
+    """Token i of src [n, hkv, d] written to position i of one contiguous
+    sequence of planes [1, hkv, n, d]; returns the planes."""
+    n, _, d = src.shape
+    planes = [_shifted(torch.full((1, hkv, n, d) if full else (1, hkv, n), 0x33, dtype=dt,
+                                  device="cuda"), wide) for dt, full in arrays]
+    kv = F.kv_view(planes[0].view(torch.int8), None,
+                   torch.tensor([n], dtype=torch.int32, device="cuda"), num_kv_heads=hkv,
+                   max_seq_len=n, k_is_layout_only=True)
+    fn(kv, _shifted(src, wide), torch.zeros(n, dtype=torch.int32, device="cuda"),
+       torch.arange(n, dtype=torch.int32, device="cuda"), planes)
+    return [p[0].transpose(0, 1).cpu().numpy() for p in planes]
+
+
+def _write_keys(kv, src, seq, pos, planes):
+    F.fold_q8_write_keys(kv, src, seq, pos, F.Q8Keys(*planes))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("hkv,n", [(1, 1), (3, 11), (1, 32), (1, 65), (5, 333), (7, 301)])
+@pytest.mark.parametrize("wide", [True, False])
+def test_key_writer_rounding(d, hkv, n, wide):
+    """Codes of keys whose quotients tie (one-hot rows, small integers), span
+    many binades or are tiny, zero or large: the oracle's, bit for bit."""
+    g = torch.Generator().manual_seed(n + d)
+    k = torch.randn(n, hkv, d, generator=g)
+    pick = torch.arange(n * hkv).view(n, hkv, 1) % 8
+    one_hot = torch.zeros(n, hkv, d).scatter_(
+        2, torch.randint(0, d, (n, hkv, 1), generator=g), 127.0)
+    few = torch.randint(-3, 4, (n, hkv, d), generator=g).float()
+    wide_span = k * torch.exp2(torch.randint(-14, 15, (n, hkv, d), generator=g).float())
+    for i, other in enumerate((one_hot, few, wide_span, torch.zeros_like(k), k * 2.0 ** -120,
+                               k * 2.0 ** 100)):
+        k = torch.where(pick == i + 1, other, k)
+    k = k.to(torch.bfloat16)
+    got = _write_all(_write_keys, k.cuda(), [(torch.int8, True), (torch.int8, True),
+                                             (torch.int16, False)], hkv, wide)
+    a, b, e = q8.split_keys(host_bits(k))
+    assert np.array_equal(got[0], a) and np.array_equal(got[1], b)
+    assert np.array_equal(got[2].view(np.uint16), e)
+
+
+def test_key_writer_keeps_non_finite_keys_to_themselves():
+    """A key with an infinity or a NaN changes no other key's code; a NaN key
+    is stored as zero."""
+    k = torch.randn(40, 2, 128).to(torch.bfloat16)
+    clean = _write_all(_write_keys, k.cuda(), [(torch.int8, True), (torch.int8, True),
+                                               (torch.int16, False)], 2, True)
+    k[7, 0, 5], k[21, 1, 100], k[22, 0, 0] = float("inf"), float("nan"), float("-inf")
+    got = _write_all(_write_keys, k.cuda(), [(torch.int8, True), (torch.int8, True),
+                                             (torch.int16, False)], 2, True)
+    ok = np.ones((40, 2), dtype=bool)
+    ok[7, 0] = ok[21, 1] = ok[22, 0] = False
+    for x, y in zip(got, clean):
+        assert np.array_equal(x[ok], y[ok])
+    assert not got[0][21, 1].any() and not got[1][21, 1].any() and got[2][21, 1] == 0
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("scale_exp", [-6, 0, 3])
+@pytest.mark.parametrize("wide", [True, False])
+def test_value_writer_every_bf16(d, scale_exp, wide):
+    """The E4M3 planes of every BF16 pattern (NaN codes only checked to be the
+    saturated ones), of 3 heads' rows."""
+    bits = torch.arange(65536, dtype=torch.int32).to(torch.int16)
+    pad = (-65536) % (3 * d)
+    v = torch.cat([bits, bits[:pad]]).view(torch.bfloat16).view(-1, 3, d)
+    got = _write_all(lambda kv, s, seq, pos, pl: F.fold_v8_write_values(
+        kv, s, seq, pos, F.V8Values(pl[0], pl[1], scale_exp)), v.cuda(),
+        [(torch.uint8, True), (torch.uint8, True)], 3, wide)
+    nan = torch.isnan(v.float()).numpy()
+    with np.errstate(all="ignore"):
+        p, r = q8.split_values(np.where(nan, 0, host_bits(v)).astype(np.uint16), scale_exp)
+    assert np.array_equal(got[0][~nan], p[~nan]) and np.array_equal(got[1][~nan], r[~nan])
+    assert ((got[0][nan] & 0x7F) == 0x7E).all()
