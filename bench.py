@@ -679,8 +679,9 @@ def q8_kernel_name(wl, values8):
     v8 = "true" if values8 else "false"
     if wl.group == 1:
         return f"decode_q8_split_kernel<{wl.head_dim}, true, false, {v8}, 4>"
-    if wl.group <= 8:
-        return f"decode_q8_packed_kernel<{wl.head_dim}, 2, true, false, {v8}>"
+    if wl.group <= 16:
+        pack = 2 if wl.group <= 8 else 1
+        return f"decode_q8_rows_kernel<{wl.head_dim}, {pack}, true, false, {v8}>"
     return f"decode_q8_kernel<{wl.head_dim}, ..., true, false, {v8}>"
 
 

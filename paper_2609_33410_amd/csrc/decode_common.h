@@ -89,22 +89,23 @@ __device__ __forceinline__ ScanPlace scan_place(const DecodeArgs& a) {
 // longest sequences start first and the last to start are the shortest ones:
 // a ragged batch drains with less of the call left to a half-empty chip.
 // Which workgroup scans which keys changes nothing else (same sums, same
-// bits).  Every thread of the workgroup must call it (one barrier).
+// bits).  Every wave ranks the lengths itself, lane i for sequence i: one load
+// and num_seqs readlanes, no LDS and no barrier.  (Ranked by a loop of scalar
+// loads, one round trip each, 32 sequences cost a workgroup microseconds
+// before its first key load.)
 
-__device__ __forceinline__ ScanPlace scan_place_by_length(const DecodeArgs& a, int* order) {
+__device__ __forceinline__ ScanPlace scan_place_by_length(const DecodeArgs& a) {
+  static_assert(kOrderMax <= 64, "a lane per sequence");
   const ScanGeometry& g = a.geo;
   const int cap = view_capacity(g);
-  if (static_cast<int>(threadIdx.x) < g.num_seqs) {
-    const int i = threadIdx.x;
-    const int li = clamp_len(g.seq_lens[i], cap);
-    int r = 0;
-    for (int j = 0; j < g.num_seqs; ++j) {
-      const int lj = clamp_len(g.seq_lens[j], cap);
-      r += (lj > li || (lj == li && j < i)) ? 1 : 0;
-    }
-    order[r] = i;
+  const int lane = threadIdx.x & 63;
+  const bool mine = lane < g.num_seqs;
+  const int li = mine ? clamp_len(g.seq_lens[lane], cap) : -1;
+  int r = 0;
+  for (int j = 0; j < g.num_seqs; ++j) {
+    const int lj = __builtin_amdgcn_readlane(li, j);
+    r += (lj > li || (lj == li && j < lane)) ? 1 : 0;
   }
-  __syncthreads();
   ScanPlace p;
   int bid = blockIdx.x;
   p.kvh = bid % g.hkv;
@@ -113,10 +114,11 @@ __device__ __forceinline__ ScanPlace scan_place_by_length(const DecodeArgs& a, i
   bid /= a.num_splits;
   const int rank = bid % g.num_seqs;
   p.rg = bid / g.num_seqs;
-  p.seq = __builtin_amdgcn_readfirstlane(order[rank]);
+  const uint64_t hit = __builtin_amdgcn_ballot_w64(mine && r == rank);  // one lane
+  p.seq = hit ? __builtin_ctzll(hit) : 0;
   p.req0 = p.seq;
   p.nrows = g.group;
-  p.n = clamp_len(ld_uniform(g.seq_lens, p.seq), cap);
+  p.n = __builtin_amdgcn_readlane(li, p.seq);
   p.nchunks = (p.n + kChunk - 1) / kChunk;
   return p;
 }

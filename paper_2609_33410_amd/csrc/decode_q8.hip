@@ -1,8 +1,10 @@
 // Gated split-KV decode over a two-plane INT8 key cache (Section 4, "Cache
 // format", "Weight-gated reads", "Value product"; Algorithm 1 with BF16 values).
 //
-// Workgroup = (kv sequence, kv head, split, read group of 16*RB query rows);
-// four wave64s; wave w owns 16-key chunk 4t + w of each 64-key tile t of its
+// Read groups of 32 rows (more than 16 rows on a kv sequence: wide draft
+// levels, cascade prefixes); decode_q8_rows.hip serves 2 to 16 rows and
+// decode_q8_split.hip one.  Workgroup = (kv sequence, kv head, split, read
+// group of 16*RB query rows, RB = 2); four wave64s; wave w owns 16-key chunk 4t + w of each 64-key tile t of its
 // split, as in the BF16 scan.  Per chunk and 16-row block:
 //
 //   coarse   c_aa = A_keys . Qa^T and c_ab = A_keys . Qb^T with
@@ -519,25 +521,21 @@ template <int D>
 hipError_t launch_q8_d(const Q8DecodeArgs& a, unsigned blocks, hipStream_t stream) {
   const bool dbg = a.d.x_out || a.d.key_gate_out || a.d.page_gate_out || a.xc_out ||
                    a.refine_gate_out || a.refine_v_gate_out;
-  const int rb = a.d.rows_per_group / 16;
-  const bool v8 = a.vp != nullptr;
-  if (rb == 1) return v8 ? launch_q8_v<D, 1, true>(a, dbg, blocks, stream)
-                         : launch_q8_v<D, 1, false>(a, dbg, blocks, stream);
-  if (rb == 2) return v8 ? launch_q8_v<D, 2, true>(a, dbg, blocks, stream)
-                         : launch_q8_v<D, 2, false>(a, dbg, blocks, stream);
-  return hipErrorInvalidValue;
+  if (a.d.rows_per_group != 32) return hipErrorInvalidValue;
+  return a.vp ? launch_q8_v<D, 2, true>(a, dbg, blocks, stream)
+              : launch_q8_v<D, 2, false>(a, dbg, blocks, stream);
 }
 
 }  // namespace
 
-hipError_t launch_q8_decode_packed(const Q8DecodeArgs& a, int head_dim, hipStream_t stream);
+hipError_t launch_q8_decode_rows(const Q8DecodeArgs& a, int head_dim, hipStream_t stream);
 hipError_t launch_q8_decode_valu(const Q8DecodeArgs& a, int head_dim, hipStream_t stream);
 
 hipError_t launch_q8_decode(const Q8DecodeArgs& a, int head_dim, hipStream_t stream) {
   // one row per kv sequence and head: the VALU scan
   if (a.d.rows_per_group == 1) return launch_q8_decode_valu(a, head_dim, stream);
-  // at most eight rows per kv sequence: several chunks per pass
-  if (a.d.rows_per_seq <= 8) return launch_q8_decode_packed(a, head_dim, stream);
+  // at most 16 rows per kv sequence: key stream and gathered live keys
+  if (a.d.rows_per_seq <= 16) return launch_q8_decode_rows(a, head_dim, stream);
   const long long blocks = static_cast<long long>(a.d.geo.num_seqs) * a.d.geo.hkv *
                            a.d.num_splits * a.d.row_groups;
   if (blocks == 0) return hipSuccess;

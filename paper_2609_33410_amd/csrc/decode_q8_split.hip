@@ -288,8 +288,7 @@ void decode_q8_split_kernel(const Q8DecodeArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   sc.part = sc.lane % S::LPK;
   sc.kslot = sc.lane / S::LPK;
-  __shared__ int order[kOrderMax];
-  sc.p = a.d.by_length ? scan_place_by_length(a.d, order) : scan_place(a.d);
+  sc.p = a.d.by_length ? scan_place_by_length(a.d) : scan_place(a.d);
   if (sc.p.rg >= sc.p.nrows) return;  // uniform: no row
   sc.pshift = q8_page_shift(g);
   sc.gate_row = (static_cast<size_t>(sc.p.seq) * g.hkv + sc.p.kvh) * a.d.row_groups + sc.p.rg;

@@ -154,8 +154,7 @@ __global__ __launch_bounds__(64 * W) void decode_split_kernel(const DecodeArgs a
   sc.part = sc.lane % S::LPK;
   sc.kslot = sc.lane / S::LPK;
 
-  __shared__ int order[kOrderMax];
-  const ScanPlace pl = a.by_length ? scan_place_by_length(a, order) : scan_place(a);
+  const ScanPlace pl = a.by_length ? scan_place_by_length(a) : scan_place(a);
   sc.seq = pl.seq;
   sc.kvh = pl.kvh;
   const int split = pl.split;

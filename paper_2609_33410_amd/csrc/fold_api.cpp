@@ -841,7 +841,7 @@ fold_status fold_q8_decode_split(const fold_kv_view* kv, const fold_q8_keys* key
   a.d.rows_per_seq = rows;
   a.d.rows_per_group = gr;
   a.d.row_groups = groups;
-  a.d.by_length = (gr == 1 && !kv->row_indptr && kv->num_seqs >= 2 &&
+  a.d.by_length = (rows <= 16 && !kv->row_indptr && kv->num_seqs >= 2 &&
                    kv->num_seqs <= fold::kOrderMax) ? 1 : 0;
   a.keys = {keys->plane_a, keys->plane_b, keys->scale};
   a.qp = q->planes;

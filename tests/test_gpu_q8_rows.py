@@ -1,0 +1,71 @@
+"""The two-plane scan of 2 to 16 rows at the sizes where its stream, list and
+in-place refinement can go wrong: block-table windows of 64 chunks a wave, odd
+steps, odd pages and unaligned contiguous rows, packed and unpacked row counts,
+steps that list a few keys and steps that refine them all."""
+
+import pytest
+import torch
+
+import paper_2609_33410_amd as F
+from tests import _gpu_q8
+from tests.test_gpu_q8 import INF, _full_parity
+from tests.test_gpu_v8 import _v8_parity
+from workloads import make_cascade, make_custom
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    F.load_library()
+
+
+@pytest.mark.parametrize("d,group,page", [(64, 2, 48), (128, 4, 16), (128, 16, 32), (64, 16, 16)])
+def test_windows_and_odd_steps(d, group, page):
+    """One split of 4096 + 16 k keys: a wave's second window starts with its
+    65th chunk; chunk counts leave whole, odd and partial last steps."""
+    lens = [4095, 4097, 4160, 4096 + 16 * 5 + 3, 31]
+    wl = make_custom(batch=len(lens), heads=group, kv_heads=1, dim=d, lens=lens, page_size=page,
+                     spike_count=30, n_sink=1, seed=d + group, device="cuda")
+    for T, kappa in ((INF, -4.0), (16.0, -4.0), (8.0, 3.0)):
+        _full_parity(wl, T, kappa=kappa, splits=[1], own_mode=False)
+
+
+@pytest.mark.parametrize("group", [2, 8, 16])
+@pytest.mark.parametrize("kappa", [-8.0, 0.0, 2.0, INF])
+def test_listed_and_refined_in_place(group, kappa):
+    """Refine thresholds from a key here and there to every key: list entries
+    that wrap, gathers inside the stream, steps refined in place; 8-bit values
+    with their second plane through both."""
+    lens = [700, 1337]
+    wl = make_custom(batch=2, heads=2 * group, kv_heads=2, dim=128, lens=lens, spike_count=40,
+                     n_sink=2, seed=int(group + 10 * min(kappa, 9.0)) % 97, device="cuda")
+    for T in (INF, 16.0, 5.0):
+        _full_parity(wl, T, kappa=kappa, splits=[2], own_mode=False)
+        _v8_parity(wl, T, kappa_v=kappa, splits=[2])
+
+
+@pytest.mark.parametrize("requests,heads,kv_heads", [(2, 8, 2), (3, 8, 2), (3, 4, 1), (4, 8, 2),
+                                                     (5, 2, 1)])
+def test_stacked_rows_around_eight(requests, heads, kv_heads):
+    """Levels of 8, 12 and 16 stacked rows (and 10): several requests' GQA
+    groups in one row block, packed two chunks a pass up to eight rows."""
+    wl = make_cascade(requests=requests, heads=heads, kv_heads=kv_heads, dim=64, prefix_len=816,
+                      suffix_len=32, splits=(2, 1), seed=requests + heads, device="cuda")
+    for T in (INF, 10.0):
+        _full_parity(wl, T, kappa=1.0, own_mode=False)
+
+
+@pytest.mark.parametrize("T", [INF, 16.0])
+def test_a_page_outside_the_pool_touches_its_sequence_only(T):
+    wl = make_custom(batch=3, heads=8, kv_heads=2, dim=128, lens=[400, 333, 200], spike_count=5,
+                     n_sink=1, seed=8, device="cuda")
+    res, keys = _gpu_q8.run(wl, T, kappa=-4.0, splits=[2])
+    for lv in wl.levels:
+        lv.block_table[1, 3], lv.block_table[1, 9] = -1, 10 ** 6
+    bad, _ = _gpu_q8.run(wl, T, kappa=-4.0, splits=[2], keys=keys, z=res["z"].cuda())
+    for r in (0, 2):
+        assert torch.equal(bad["out"][r], res["out"][r])
+    assert torch.isfinite(bad["out"][1]).all()
