@@ -242,6 +242,24 @@ __global__ __launch_bounds__(kStkThreads) void decode_stacked_kernel(const Decod
   uint32_t tmeta = 0;
   int sreq = -1;
   uint32_t slen = 0, sbt = 0;
+  // CASC: and from these, formed by the lane once, the byte offset of the
+  // wave's chunk of tile j in the caches and how many bytes of it exist (0:
+  // none, or a page outside the pool).  A fetch then reads three lanes.  A
+  // tile's instructions bound this kernel (two waves a SIMD, 1.3 us a tile
+  // whatever the LDS reads' order): formed per fetch on the scalar unit, the
+  // 64-bit products were over a hundred of some 400 a wave issued per tile.
+  // 64 requests, 16384 shared and 1024 own keys, 8 + 4 tiles a workgroup:
+  // 25.2 -> 23.4 us.
+  uint32_t toff_lo = 0, toff_hi = 0, tbytes = 0;
+  auto place_tiles = [&]() {
+    const int have = min(kChunk, static_cast<int>(tmeta & 0xFFu) - kChunk * my_chunk);
+    const bool ok = have > 0 && ptab >= 0 && ptab < g.num_pages;
+    const uint64_t off = ((static_cast<uint64_t>(ok ? ptab : 0) * g.hkv + p.kvh) * g.page_size +
+                          (tmeta >> 16)) * KEYB;
+    toff_lo = static_cast<uint32_t>(off);
+    toff_hi = static_cast<uint32_t>(off >> 32);
+    tbytes = ok ? static_cast<uint32_t>(have) * KEYB : 0u;
+  };
   auto load_ptab = [&](int base) {
     ptab_base = base;
     const int jj = base + lane;
@@ -261,6 +279,7 @@ __global__ __launch_bounds__(kStkThreads) void decode_stacked_kernel(const Decod
       } else if (jj >= m_pre && jj < m) {
         sreq = ld_uniform(g.row_req, p.req0 + pos_lo + (p.split + (jj - m_pre) * S) / a.sfx_tiles);
       }
+      place_tiles();
     } else {
       ptab = jj < m && c < p.nchunks
                  ? g.block_table[static_cast<size_t>(p.seq) * g.max_pages + (c * kChunk) / g.page_size]
@@ -268,6 +287,7 @@ __global__ __launch_bounds__(kStkThreads) void decode_stacked_kernel(const Decod
     }
   };
   auto page_of = [&](int j) -> int {
+    if constexpr (CASC) return 0;  // its tiles are placed by load_ptab
     if (j >= m || g.page_size <= 0) return 0;
     if ((j & ~(kWaveSize - 1)) != ptab_base) {
       load_ptab(j & ~(kWaveSize - 1));
@@ -300,15 +320,17 @@ __global__ __launch_bounds__(kStkThreads) void decode_stacked_kernel(const Decod
                 (static_cast<uint32_t>(pl_sfx) << 8) |
                 (static_cast<uint32_t>(key0 - pidx * g.page_size) << 16);
       }
+      place_tiles();
     }
   };
-  // Block-table entries of tiles 0..4, read (and the page-table load waited
-  // for) before the assembly loads below are issued; the empty asm pins that
-  // order.
-  int pg0 = page_of(0), pg1 = page_of(1), pg2 = page_of(2), pg3 = page_of(3),
+  // Block-table entries of tiles 0..4 (CASC: the placed tiles), read (and the
+  // page-table load waited for) before the assembly loads below are issued;
+  // the empty asm pins that order.
+  const int pg0 = page_of(0), pg1 = page_of(1), pg2 = page_of(2), pg3 = page_of(3),
             pg4 = page_of(4);
   asm volatile("" : : "s"(pg0), "s"(pg1), "s"(pg2), "s"(pg3), "s"(pg4));
   if constexpr (CASC) {
+    asm volatile("" : "+v"(toff_lo), "+v"(toff_hi), "+v"(tbytes) : : "memory");
     const int32_t* lp = a.sfx_seq_lens;
     const int32_t* bp = a.sfx_block_table;
     if (lane >= m_pre && lane < m) {
@@ -326,11 +348,6 @@ __global__ __launch_bounds__(kStkThreads) void decode_stacked_kernel(const Decod
     if (m_pre < 5 && m > m_pre) {  // a suffix tile among the first five: wait here
       wait_vmcnt<0>();
       settle_sfx();
-      pg0 = page_of(0);
-      pg1 = page_of(1);
-      pg2 = page_of(2);
-      pg3 = page_of(3);
-      pg4 = page_of(4);
     }
   }
   u32x4 qb[NK];
@@ -417,13 +434,12 @@ __global__ __launch_bounds__(kStkThreads) void decode_stacked_kernel(const Decod
   // Buffer resource words of this wave's chunk of local tile j (K or V).
   auto chunk_words = [&](int j, int phys, bool val) -> u32x4 {
     if constexpr (CASC) {
-      const uint32_t meta =
-          j < m ? static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(tmeta), j)) : 0u;
-      const int have = min(kChunk, static_cast<int>(meta & 0xFFu) - kChunk * my_chunk);
-      const bool ok = have > 0 && phys >= 0 && phys < g.num_pages;
-      const size_t off = ((static_cast<size_t>(ok ? phys : 0) * g.hkv + p.kvh) * g.page_size +
-                          (meta >> 16)) * D;
-      return rsrc_words((val ? g.v : g.k) + off, ok ? static_cast<uint32_t>(have) * KEYB : 0u);
+      // j < m <= 64: a lane of the table
+      auto at = [&](uint32_t v) {
+        return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), j));
+      };
+      const uint64_t off = (static_cast<uint64_t>(at(toff_hi)) << 32) | at(toff_lo);
+      return rsrc_words(reinterpret_cast<const unsigned char*>(val ? g.v : g.k) + off, at(tbytes));
     }
     const int c = chunk_of(j);
     uint32_t bytes = 0;
