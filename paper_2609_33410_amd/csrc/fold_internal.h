@@ -12,7 +12,7 @@ namespace fold {
 constexpr int kTile = 64;
 constexpr int kChunk = 16;
 // Largest per-request view whose scan dispatches its sequences by decreasing
-// length (each workgroup ranks the lengths itself).
+// length (each wave ranks the lengths itself).
 constexpr int kOrderMax = 64;
 
 struct ScanGeometry {
