@@ -69,3 +69,39 @@ def test_a_page_outside_the_pool_touches_its_sequence_only(T):
     for r in (0, 2):
         assert torch.equal(bad["out"][r], res["out"][r])
     assert torch.isfinite(bad["out"][1]).all()
+
+
+@pytest.mark.parametrize("group,d", [(2, 128), (8, 64), (8, 128), (16, 128), (16, 64)])
+@pytest.mark.parametrize("kappa", [-4.0, INF])
+@pytest.mark.parametrize("T", [INF, 16.0])
+def test_an_infinite_value_stays_infinite(group, d, kappa, T):
+    """A refined key (listed at kappa = -4, refined in place at inf) and, at
+    full depth, one that is not, each with an infinite value in a channel of its
+    own: those channels of the rows that weigh the key are infinite, as 0 times
+    infinity must enter no sum, and every other output keeps its bits."""
+    wl = make_custom(batch=2, heads=2 * group, kv_heads=2, dim=d, lens=[700, 333],
+                     spike_count=6, n_sink=1, seed=group + d, device="cuda")
+    ref, keys = _gpu_q8.run(wl, T, kappa=kappa, splits=[2], debug=True)
+    clean, _ = _gpu_q8.run(wl, T, kappa=kappa, splits=[2], keys=keys)
+    bits = ref["dbg"][0]["refine_gate_out"][0, 1, 0, :700]
+    refined = int((bits == 1).nonzero()[0])
+    plain = int((bits == 0).nonzero()[0]) if kappa < INF and T == INF else None
+    x = ref["dbg"][0]["x_out"][0, group:]  # request 0, kv head 1
+    assert bool((x[:, refined] > -60).all()) or T < INF
+    hit = {5: refined, 9: plain}
+    for ch, key in hit.items():
+        if key is not None:
+            page = int(wl.levels[0].block_table[0, key // wl.page_size])
+            wl.v[page, 1, key % wl.page_size, ch] = float("inf") if ch == 5 else float("-inf")
+    got, _ = _gpu_q8.run(wl, T, kappa=kappa, splits=[2], keys=keys)
+    out, want = got["out"], clean["out"].clone()
+    if T == INF:
+        want[0, group:, 5] = float("inf")
+        if plain is not None:
+            want[0, group:, 9] = float("-inf")
+        assert torch.equal(out, want)
+    else:  # a row that cuts the key shares the group's read: its channel is left out
+        live = x[:, refined] >= -T
+        assert live.any() and bool((out[0, group:, 5][live] == float("inf")).all())
+        want[0, group:, 5] = out[0, group:, 5] = 0.0
+        assert torch.equal(out, want)
