@@ -130,7 +130,7 @@ struct Q8Rows {
   unsigned char* tile;
   float* list_x;      // [kListKeys][BW] coarse x
   uint32_t* list_row; // cache row, or kNoRow
-  float* list_e;      // key scale
+  float* list_e;      // key scale / 256
   int* list_key;      // key index (debug)
   int head, count;    // the list: slots head .. head + count - 1 (mod kListKeys)
 
@@ -140,7 +140,7 @@ struct Q8Rows {
   // Of row n16 % BW: the row a lane weighs, and in the lanes of a row of its
   // own (n16 < BW, the only ones with rok) that row.
   bool pok;
-  float zp, etap;          // Z (+inf for no row), eta / 256
+  float zp, etap;          // Z (+inf for no row), eta
   float ntau, ntau_v;      // -tau
   float thr;               // the score from which a key is refined
   size_t xrow, prow;       // query rows of n16 and n16 % BW (debug)
@@ -425,9 +425,11 @@ struct Q8Rows {
       // would be waited for there
       uint16_t sc0 = s.sc[PK == 2 ? 0 : b], sc1 = s.sc[PK == 2 ? 1 : b];
       asm volatile("" : "+v"(sc0), "+v"(sc1));
-      const float sc = bf16_lo(PK == 2 ? static_cast<uint32_t>(sc0) | sc1 : sc0);
-      // the scale of key 4(l/16)+i sits in lane i of the quad; etap = eta / 256;
-      // -inf in the lanes of no row (zp = +inf there)
+      // 1/256 for the products' unit goes to the key scale: its eight significant
+      // bits stay exact down to the smallest BF16, where eta's 24 would not
+      const float sc = bf16_lo(PK == 2 ? static_cast<uint32_t>(sc0) | sc1 : sc0) * (1.0f / 256.0f);
+      // the scale of key 4(l/16)+i sits in lane i of the quad; -inf in the lanes
+      // of no row (zp = +inf there)
       x[b][0] = __builtin_fmaf(etap * quad_lane<0>(sc), static_cast<float>(t[b][0]), -zp);
       x[b][1] = __builtin_fmaf(etap * quad_lane<1>(sc), static_cast<float>(t[b][1]), -zp);
       x[b][2] = __builtin_fmaf(etap * quad_lane<2>(sc), static_cast<float>(t[b][2]), -zp);
@@ -931,7 +933,7 @@ void decode_q8_rows_kernel(const Q8DecodeArgs a) {
     const int src = (sc.lane & ~15) | (sc.n16 % S::BW);
     sc.pok = __shfl(static_cast<int>(sc.rok), src, 64) != 0;
     sc.zp = __shfl(z, src, 64);
-    sc.etap = __shfl(eta, src, 64) * (1.0f / 256.0f);
+    sc.etap = __shfl(eta, src, 64);
     sc.ntau = __shfl(nt, src, 64);
     sc.ntau_v = __shfl(ntv, src, 64);
     // a key is refined when some row reaches a threshold and some row is live

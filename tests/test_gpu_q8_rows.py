@@ -3,14 +3,16 @@ in-place refinement can go wrong: block-table windows of 64 chunks a wave, odd
 steps, odd pages and unaligned contiguous rows, packed and unpacked row counts,
 steps that list a few keys and steps that refine them all."""
 
+import numpy as np
 import pytest
 import torch
 
 import paper_2609_33410_amd as F
-from tests import _gpu_q8
+from oracle import q8_oracle as q8
+from tests import _adapt, _gpu_q8
 from tests.test_gpu_q8 import INF, _full_parity
 from tests.test_gpu_v8 import _v8_parity
-from workloads import make_cascade, make_custom
+from workloads import host_bits, make_cascade, make_custom
 
 pytestmark = pytest.mark.gpu
 
@@ -105,3 +107,27 @@ def test_an_infinite_value_stays_infinite(group, d, kappa, T):
         assert live.any() and bool((out[0, group:, 5][live] == float("inf")).all())
         want[0, group:, 5] = out[0, group:, 5] = 0.0
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("group", [4, 16])
+@pytest.mark.parametrize("kappa", [-4.0, INF])
+def test_scores_of_a_tiny_query_scale(group, kappa):
+    """Queries of 2^-112 on keys of 2^112: eta is near 2^-123, the smallest
+    scale FP32 holds in full, and keeps all its bits (L to 2e-5)."""
+    wl = make_custom(batch=2, heads=2 * group, kv_heads=2, dim=128, lens=[500, 333],
+                     spike_count=6, n_sink=1, seed=group, device="cuda")
+    wl.q = (wl.q.float() * 2.0 ** -112).to(torch.bfloat16)
+    wl.k = (wl.k.float() * 2.0 ** 112).to(torch.bfloat16)
+    oi = _adapt.oracle_inputs(wl)
+    res, keys = _gpu_q8.run(wl, INF, kappa=kappa, splits=[2])
+    eta = res["eta"]
+    assert eta.min() >= 2.0 ** -126 and eta.max() < 2.0 ** -118
+    planes = q8.split_keys(host_bits(wl.k))
+    qa, qb, eta = q8.split_queries(host_bits(wl.q), wl.sm_scale)
+    tau = np.array([q8.refine_tau(n, kappa) for n in wl.flat.seq_lens_host], dtype=np.float32)
+    _, pl = q8.decode_level_q8(qa, qb, eta, planes, oi["v_bits"], num_kv_heads=2,
+                               page_size=wl.page_size, z=res["z"].double().numpy(), T=INF, tau=tau,
+                               num_splits=2, **oi["levels"][0])
+    got = res["part_L"].double().numpy()
+    print("  L error", np.abs(got / pl - 1).max())
+    assert np.allclose(got, pl, rtol=2e-5, atol=0)
