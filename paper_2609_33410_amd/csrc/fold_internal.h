@@ -105,6 +105,8 @@ struct MeanArgs {
   const int32_t* tok_pos;
   int n_tok;
   int max_blocks;         // block means: row stride in blocks
+  int first_item;         // request means: the launch's (sequence, kv head) pairs
+  unsigned num_items;
 };
 
 // Virtual rows of the block model: adds sum over the split's tiles t of

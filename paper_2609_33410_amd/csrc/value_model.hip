@@ -51,15 +51,18 @@ constexpr int kMeanThreads = 64 * kMeanWaves;
 
 constexpr int kMeanSeg = 32;      // channels per workgroup
 constexpr int kMeanInFlight = 8;  // chunk loads in flight per lane
+// (sequence, kv head) pairs per launch: a launch stays below 2^32 threads, and
+// a pair takes up to four workgroups of 1024.
+constexpr long long kMeanLaunchItems = 1 << 19;
+static_assert(kMeanLaunchItems * (128 / kMeanSeg) * kMeanThreads < (1ll << 32), "launch size");
 
 // WIDE: v is 16-byte aligned (one 16-byte load per lane); else eight 2-byte
 // loads.
 template <int D, bool WIDE>
 __global__ __launch_bounds__(kMeanThreads) void value_mean_kernel(const MeanArgs a) {
   const ScanGeometry& g = a.geo;
-  const int items = g.num_seqs * g.hkv;
-  const int item = blockIdx.x % items;
-  const int seg = blockIdx.x / items;
+  const int item = a.first_item + static_cast<int>(blockIdx.x % a.num_items);
+  const int seg = blockIdx.x / a.num_items;
   const int seq = item / g.hkv;
   const int kvh = item % g.hkv;
   const int lane = threadIdx.x & 63;
@@ -377,14 +380,23 @@ hipError_t launch_block_model(const BlockModelArgs& a, int head_dim, hipStream_t
 
 hipError_t launch_value_mean(const MeanArgs& a, int head_dim, hipStream_t stream) {
   if (head_dim != 64 && head_dim != 128) return hipErrorInvalidValue;
-  const long long blocks =
-      static_cast<long long>(a.geo.num_seqs) * a.geo.hkv * (head_dim / kMeanSeg);
-  if (blocks == 0) return hipSuccess;
+  const long long items = static_cast<long long>(a.geo.num_seqs) * a.geo.hkv;
   const bool wide = (reinterpret_cast<uintptr_t>(a.geo.v) & 15u) == 0;
-  const unsigned grid = static_cast<unsigned>(blocks);
-  if (head_dim == 128)
-    return wide ? launch_mean<128, true>(a, grid, stream) : launch_mean<128, false>(a, grid, stream);
-  return wide ? launch_mean<64, true>(a, grid, stream) : launch_mean<64, false>(a, grid, stream);
+  const int segs = head_dim / kMeanSeg;
+  MeanArgs part = a;
+  for (long long first = 0; first < items; first += kMeanLaunchItems) {
+    const long long n = items - first < kMeanLaunchItems ? items - first : kMeanLaunchItems;
+    part.first_item = static_cast<int>(first);
+    part.num_items = static_cast<unsigned>(n);
+    const unsigned grid = static_cast<unsigned>(n * segs);
+    const hipError_t e =
+        head_dim == 128 ? (wide ? launch_mean<128, true>(part, grid, stream)
+                                : launch_mean<128, false>(part, grid, stream))
+                        : (wide ? launch_mean<64, true>(part, grid, stream)
+                                : launch_mean<64, false>(part, grid, stream));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_value_mean_append(const MeanArgs& a, int head_dim, hipStream_t stream) {

@@ -89,6 +89,27 @@ def test_value_mean_skips_pages_outside_the_pool():
         assert (got[r] - want / n).abs().max().item() < 5e-6
 
 
+@pytest.mark.parametrize("d,seqs", [(128, (1 << 14) + 1), (64, (1 << 15) + 1)])
+def test_value_mean_of_more_pairs_than_one_launch_holds(d, seqs):
+    """64 heads of just over 2^14 (D = 64: 2^15) sequences: four (two)
+    workgroups of 1024 threads a pair would pass the 2^32 threads of a launch.
+    Rows of at most 16 keys, on one of four pages."""
+    hkv, page = 64, 16
+    g = torch.Generator(device="cuda").manual_seed(d)
+    v = torch.randn(4, hkv, page, d, generator=g, device="cuda").to(torch.bfloat16)
+    bt = torch.randint(0, 4, (seqs, 1), generator=g, device="cuda").to(torch.int32)
+    lens = torch.randint(0, page + 1, (seqs,), generator=g, device="cuda").to(torch.int32)
+    kv = F.kv_view(v, v, lens, num_kv_heads=hkv, max_seq_len=page, block_table=bt)
+    got = F.fold_value_mean(kv, torch.full((seqs, hkv, d), 7.0, device="cuda"))
+    sums = torch.cat([torch.zeros_like(v[:, :, :1]).double(), v.double().cumsum(2)], 2)
+    want = (sums / torch.arange(page + 1, device="cuda").clamp(min=1)[:, None]).float()
+    want = want.transpose(1, 2).contiguous()  # [page, length, hkv, d]
+    for i in range(0, seqs, 1 << 12):
+        part = slice(i, min(i + (1 << 12), seqs))
+        err = got[part] - want[bt[part, 0].long(), lens[part].long()]
+        assert err.abs().max().item() < 5e-6, i
+
+
 @pytest.mark.parametrize("d,hkv,n_tok", [(128, 3, 1), (128, 8, 2048), (128, 8, 2049), (64, 5, 6554),
                                          (64, 1, 32769), (128, 7, 2341)])
 @pytest.mark.parametrize("which", ["kv", "k", "v"])
