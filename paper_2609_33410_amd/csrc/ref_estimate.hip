@@ -65,10 +65,11 @@ hipError_t launch_q8_estimate(const Q8EstimateArgs& a, int head_dim, hipStream_t
 // The fused front: a wave per row (four waves at least), so that each wave
 // splits (and later reduces) one row: the FP64 rotation of a second row behind
 // the first is what groups of 16 waited for (12.7 us with eight waves, 11.2
-// with sixteen, for 32 requests x 2 groups at D = 128).
+// with sixteen, for 32 requests x 2 groups at D = 128).  Sixteen waves only
+// where the launch stays below 2^32 threads.
 template <int D>
 void launch_front_d(const Q8EstimateArgs& a, unsigned blocks, hipStream_t stream) {
-  if (a.e.geo.group > 8)
+  if (a.e.geo.group > 8 && blocks < (1ull << 32) / (4 * kThreads))
     hipLaunchKernelGGL((estimate_kernel<D, true, true, 4 * kThreads>), dim3(blocks),
                        dim3(4 * kThreads), 0, stream, a);
   else if (a.e.geo.group > 4)

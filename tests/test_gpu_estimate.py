@@ -45,3 +45,38 @@ def test_samples_match_the_oracle(strata, page, group, d):
                         seq_lens=oi["flat"]["seq_lens"], block_table=oi["flat"]["block_table"],
                         p=params)
     assert np.abs(z.cpu().double().numpy() - zo).max() <= 1e-3
+
+
+def test_front_of_more_groups_than_sixteen_waves_allow():
+    """2^22 groups of 16 rows: workgroups of 1024 threads would reach 2^32
+    threads, past a launch's limit.  64 requests' queries repeated: every
+    repetition has the codes, eta, tau and Z of the 64 alone."""
+    reqs, heads, hkv, d, rep = 64, 1024, 64, 64, 1 << 10
+    g = torch.Generator(device="cuda").manual_seed(22)
+    k = torch.randn(64 * 64, hkv, d, generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn(reqs, heads, d, generator=g, device="cuda").to(torch.bfloat16)
+    lens = torch.randint(0, 65, (reqs,), generator=g, device="cuda").to(torch.int32)
+    bt = torch.randint(0, 256, (reqs, 4), generator=g, device="cuda").to(torch.int32)
+    plane = torch.empty(256, hkv, 16, d, dtype=torch.int8, device="cuda")
+    keys = F.Q8Keys(plane, torch.empty_like(plane),
+                    torch.empty(256, hkv, 16, dtype=torch.int16, device="cuda"))
+    pool = F.kv_view(plane, None, torch.full((256,), 16, dtype=torch.int32, device="cuda"),
+                     num_kv_heads=hkv, max_seq_len=16, k_is_layout_only=True)
+    at = torch.arange(4096, device="cuda", dtype=torch.int32)
+    F.fold_q8_write_keys(pool, k, at // 16, at % 16, keys)
+
+    def front(n):
+        qn = q.repeat(n, 1, 1)
+        kv = F.kv_view(plane, None, lens.repeat(n), num_kv_heads=hkv, max_seq_len=64,
+                       block_table=bt.repeat(n, 1), k_is_layout_only=True)
+        qq = F.q8_empty_query(qn)
+        z = torch.full((n * reqs, heads), float("nan"), device="cuda")
+        F.fold_q8_front(kv, keys, qn, 0.125, qq, z, req_lens=kv.tensors[2])
+        return qq.planes, qq.eta, qq.tau, z
+
+    want = front(1)
+    assert torch.isfinite(want[3]).all()
+    for got, w in zip(front(rep), want):
+        got = got.view(rep, *w.shape)
+        for i in range(0, rep, 64):
+            assert torch.equal(got[i:i + 64], w.expand(64, *w.shape)), i
