@@ -273,6 +273,12 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# torch's own names, without a promise that they stay: a build that lacks one
+# goes by torch.cuda.current_stream().
+_RAW_STREAM = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_RAW_DEVICE = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> Optional[int]:
     # Every entry point asks for the stream: once the runtime is up the current
     # one is read as the raw handle (0.3 us with the look whether it is up),
@@ -280,8 +286,8 @@ def _stream(stream) -> Optional[int]:
     # comparing sizes as they are and naming a tensor for an error only, a
     # 512-key estimate, scan and combine take 21.7 us on the host, from 29.0.
     if stream is None:
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _RAW_STREAM is not None and _RAW_DEVICE is not None and torch.cuda.is_initialized():
+            return _RAW_STREAM(_RAW_DEVICE())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 

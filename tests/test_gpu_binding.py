@@ -33,6 +33,17 @@ def test_stream_is_the_callers_current_one():
     assert fold._stream(side) == side.cuda_stream
 
 
+@pytest.mark.parametrize("name", ["_RAW_STREAM", "_RAW_DEVICE"])
+def test_stream_without_torchs_raw_handle(name, monkeypatch):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    monkeypatch.setattr(fold, name, None)
+    torch.zeros(1, device="cuda")
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert fold._stream(None) == side.cuda_stream
+
+
 @pytest.mark.parametrize("what", ["part_A", "part_A rank", "part_L", "part_Lcut", "z", "device",
                                   "view device"])
 def test_slots_of_another_shape_or_place_are_refused(what):
