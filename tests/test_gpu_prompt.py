@@ -219,14 +219,46 @@ def test_key_writer_keeps_non_finite_keys_to_themselves():
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("wide", [True, False])
+def test_key_writer_forms_agree_on_extreme_keys(d, wide):
+    """More than 2048 rows take the row groups, fewer a wave a row: the same
+    codes and scales for infinities, NaN, the largest and the smallest values,
+    and the oracle's for every finite key beside them."""
+    inf, nan, most = float("inf"), float("nan"), 3.3895313892515355e38
+    k = torch.randn(1100, 2, d, generator=torch.Generator().manual_seed(d))
+    k[3, 0, 5], k[4, 1, d - 1] = inf, -inf
+    k[5, 0, 0], k[5, 0, 1] = inf, inf
+    k[6, 1, 2], k[6, 1, d - 3] = inf, -inf
+    k[7, 0, 9], k[8, 1, 0], k[8, 1, 4] = nan, nan, inf
+    k[9] = most
+    k[10, :, ::2], k[10, :, 1::2] = most, -most
+    k[11], k[12] = 2.0 ** -133, 2.0 ** -126
+    k[1099, 1] = inf
+    k = k.to(torch.bfloat16)
+    arrays = [(torch.int8, True), (torch.int8, True), (torch.int16, False)]
+    got = _write_all(_write_keys, k.cuda(), arrays, 2, wide)
+    few = _write_all(_write_keys, k[:40].contiguous().cuda(), arrays, 2, wide)
+    for x, y in zip(got, few):
+        assert np.array_equal(x[:40], y)
+    ok = torch.isfinite(k.float()).all(-1).numpy()
+    ok[9:11] = False  # the codes' scale passes the largest BF16
+    want = q8.split_keys(host_bits(torch.where(torch.from_numpy(ok)[..., None], k, 0)))
+    for x, y in zip(got, want):
+        assert np.array_equal(x.view(y.dtype)[ok], y[ok])
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("scale_exp", [-6, 0, 3])
 @pytest.mark.parametrize("wide", [True, False])
-def test_value_writer_every_bf16(d, scale_exp, wide):
+@pytest.mark.parametrize("copies", [1, 9])
+def test_value_writer_every_bf16(d, scale_exp, wide, copies):
     """The E4M3 planes of every BF16 pattern (NaN codes only checked to be the
-    saturated ones), of 3 heads' rows."""
+    saturated ones), of 3 heads' rows: once, the form of up to 2^19 elements,
+    and nine times, a prompt's, with a ragged last workgroup."""
     bits = torch.arange(65536, dtype=torch.int32).to(torch.int16)
-    pad = (-65536) % (3 * d)
-    v = torch.cat([bits, bits[:pad]]).view(torch.bfloat16).view(-1, 3, d)
+    pad = (-65536 * copies) % (3 * d) + (3 * d if copies > 1 else 0)
+    v = torch.cat([bits.repeat(copies), bits[:pad]]).view(torch.bfloat16).view(-1, 3, d)
+    assert (v.numel() > 2 ** 19) == (copies > 1)
     got = _write_all(lambda kv, s, seq, pos, pl: F.fold_v8_write_values(
         kv, s, seq, pos, F.V8Values(pl[0], pl[1], scale_exp)), v.cuda(),
         [(torch.uint8, True), (torch.uint8, True)], 3, wide)
