@@ -131,3 +131,38 @@ def test_scores_of_a_tiny_query_scale(group, kappa):
     got = res["part_L"].double().numpy()
     print("  L error", np.abs(got / pl - 1).max())
     assert np.allclose(got, pl, rtol=2e-5, atol=0)
+
+
+@pytest.mark.parametrize("group", [2, 8, 16])
+@pytest.mark.parametrize("values8", [False, True])
+@pytest.mark.parametrize("kappa", [-4.0, 0.0, INF])
+def test_cut_masses_of_the_production_scan(group, values8, kappa):
+    """Cut masses asked for without debug outputs, of keys that stay in the
+    stream, are listed or refined in place: the debug variant's slots bit for
+    bit, and the sum of the cut weights of its exported scores (FP32 sums of
+    at most 1337 terms: 2e-5)."""
+    wl = make_custom(batch=2, heads=2 * group, kv_heads=2, dim=128, lens=[700, 1337],
+                     spike_count=40, n_sink=2, seed=group, device="cuda")
+    keys = _gpu_q8.encode_cache(wl)
+    vals = _gpu_q8.encode_values(wl) if values8 else None
+    qq = _gpu_q8.split_query(wl, kappa, kappa)
+    levels, _ = _gpu_q8.level_views(wl, keys)
+    z = _gpu_q8.estimate(wl, keys, qq)
+    b, h, d = wl.q.shape
+
+    def scan(T, **debug):
+        out = [torch.full(s, float("nan"), device="cuda") for s in ((2, b, h, d), (2, b, h), (2, b, h))]
+        F.fold_q8_decode_split(levels[0], keys, qq, z, T, 2, 0, out[0], out[1], part_Lcut=out[2],
+                               values=vals, **debug)
+        return out
+
+    for T in (INF, 8.0):
+        x = torch.full((b, h, 1337), -INF, device="cuda")
+        want = scan(T, x_out=x)
+        got = scan(T)
+        for g, w in zip(got, want):
+            assert torch.equal(g, w)
+        x = x.double()
+        cut = torch.where(x < -T, torch.exp2(x), torch.zeros_like(x)).sum(-1)
+        assert T == INF or bool((cut > 0).all())
+        assert torch.allclose(got[2].double().sum(0), cut, rtol=2e-5, atol=0)
