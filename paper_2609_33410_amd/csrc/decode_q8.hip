@@ -4,8 +4,9 @@
 // Read groups of 32 rows (more than 16 rows on a kv sequence: wide draft
 // levels, cascade prefixes); decode_q8_rows.hip serves 2 to 16 rows and
 // decode_q8_split.hip one.  Workgroup = (kv sequence, kv head, split, read
-// group of 16*RB query rows, RB = 2); four wave64s; wave w owns 16-key chunk 4t + w of each 64-key tile t of its
-// split, as in the BF16 scan.  Per chunk and 16-row block:
+// group of 32 query rows, two blocks of 16); four wave64s; wave w owns 16-key
+// chunk 4t + w of each 64-key tile t of its split, as in the BF16 scan.  Per
+// chunk and 16-row block:
 //
 //   coarse   c_aa = A_keys . Qa^T and c_ab = A_keys . Qb^T with
 //            v_mfma_i32_16x16x64_i8 (keys on M, rows on N, channels on K;
@@ -41,6 +42,8 @@
 namespace fold {
 namespace {
 
+constexpr int RB = 2;  // 16-row blocks of a read group
+
 // 16-byte value loads per lane and chunk: BF16 rows, or one E4M3 plane.
 template <int D, bool V8>
 constexpr int kValueLoads = V8 ? D / 64 : D / 32;
@@ -54,7 +57,7 @@ struct Q8AStage {
 };
 
 // A chunk from its coarse pass to its product.
-template <int D, int RB, bool DENSE, bool V8>
+template <int D, bool DENSE, bool V8>
 struct Q8BStage {
   Q8Loc loc;
   float e[4];       // BF16 scales of keys 4(l/16)+i
@@ -69,7 +72,7 @@ struct Q8BStage {
   uint32_t rvmask;  // second-value-plane rows to read (wave-uniform)
 };
 
-template <int D, int RB, bool DENSE, bool DBG, bool V8>
+template <int D, bool DENSE, bool DBG, bool V8>
 struct Q8Scan {
   static constexpr int NKI = D / 64;          // 16-byte plane loads per lane per chunk
   static constexpr int NK = kValueLoads<D, V8>;  // 16-byte value loads per lane per chunk
@@ -78,7 +81,7 @@ struct Q8Scan {
   static constexpr int R = 16 * RB;
   static constexpr int NA = 4;                 // plane-A ring depth (chunks)
   using AS = Q8AStage<D, DENSE, V8>;
-  using BS = Q8BStage<D, RB, DENSE, V8>;
+  using BS = Q8BStage<D, DENSE, V8>;
 
   const Q8DecodeArgs& a;
   const ScanGeometry& g;
@@ -203,7 +206,7 @@ struct Q8Scan {
     s.refv = (both >> 8) & 0xFFu;
     // Unions over the read group: OR over each 16-lane row (row q holds keys
     // 4q..4q+3), then one row value per readlane; the row blocks fold together.
-    const uint32_t u = group_or16(RB == 2 ? both | (both >> 4) : both);
+    const uint32_t u = group_or16(both | (both >> 4));
     uint32_t vmask = 0, bmask = 0, rvmask = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -339,9 +342,9 @@ struct Q8Scan {
   }
 };
 
-template <int D, int RB, bool DENSE, bool DBG, bool V8>
+template <int D, bool DENSE, bool DBG, bool V8>
 __global__ __launch_bounds__(kScanThreads) void decode_q8_kernel(const Q8DecodeArgs a) {
-  using S = Q8Scan<D, RB, DENSE, DBG, V8>;
+  using S = Q8Scan<D, DENSE, DBG, V8>;
   constexpr int NKI = S::NKI;
   constexpr int R = S::R;
   constexpr int kTileBytes = kScanWaves * 16 * S::VSTRIDE;
@@ -359,7 +362,7 @@ __global__ __launch_bounds__(kScanThreads) void decode_q8_kernel(const Q8DecodeA
   sc.vt = smem + wave * 16 * S::VSTRIDE;
   sc.gate_row = (static_cast<size_t>(sc.p.seq) * g.hkv + sc.p.kvh) * a.d.row_groups + sc.p.rg;
   sc.gspan = (g.group < 16 ? g.group : 16) - 1;
-  sc.cross_b = RB == 2 && g.group > 16;
+  sc.cross_b = g.group > 16;
 
 #pragma unroll
   for (int b = 0; b < RB; ++b) {
@@ -500,21 +503,21 @@ __global__ __launch_bounds__(kScanThreads) void decode_q8_kernel(const Q8DecodeA
   }
 }
 
-template <int D, int RB, bool DENSE, bool V8>
-hipError_t launch_q8_rb(const Q8DecodeArgs& a, bool dbg, unsigned blocks, hipStream_t stream) {
+template <int D, bool DENSE, bool V8>
+hipError_t launch_q8_dense(const Q8DecodeArgs& a, bool dbg, unsigned blocks, hipStream_t stream) {
   if (dbg)
-    hipLaunchKernelGGL((decode_q8_kernel<D, RB, DENSE, true, V8>), dim3(blocks), dim3(kScanThreads),
+    hipLaunchKernelGGL((decode_q8_kernel<D, DENSE, true, V8>), dim3(blocks), dim3(kScanThreads),
                        0, stream, a);
   else
-    hipLaunchKernelGGL((decode_q8_kernel<D, RB, DENSE, false, V8>), dim3(blocks), dim3(kScanThreads),
+    hipLaunchKernelGGL((decode_q8_kernel<D, DENSE, false, V8>), dim3(blocks), dim3(kScanThreads),
                        0, stream, a);
   return hipGetLastError();
 }
 
-template <int D, int RB, bool V8>
+template <int D, bool V8>
 hipError_t launch_q8_v(const Q8DecodeArgs& a, bool dbg, unsigned blocks, hipStream_t stream) {
-  return a.d.dense ? launch_q8_rb<D, RB, true, V8>(a, dbg, blocks, stream)
-                   : launch_q8_rb<D, RB, false, V8>(a, dbg, blocks, stream);
+  return a.d.dense ? launch_q8_dense<D, true, V8>(a, dbg, blocks, stream)
+                   : launch_q8_dense<D, false, V8>(a, dbg, blocks, stream);
 }
 
 template <int D>
@@ -522,8 +525,8 @@ hipError_t launch_q8_d(const Q8DecodeArgs& a, unsigned blocks, hipStream_t strea
   const bool dbg = a.d.x_out || a.d.key_gate_out || a.d.page_gate_out || a.xc_out ||
                    a.refine_gate_out || a.refine_v_gate_out;
   if (a.d.rows_per_group != 32) return hipErrorInvalidValue;
-  return a.vp ? launch_q8_v<D, 2, true>(a, dbg, blocks, stream)
-              : launch_q8_v<D, 2, false>(a, dbg, blocks, stream);
+  return a.vp ? launch_q8_v<D, true>(a, dbg, blocks, stream)
+              : launch_q8_v<D, false>(a, dbg, blocks, stream);
 }
 
 }  // namespace
@@ -534,7 +537,7 @@ hipError_t launch_q8_decode_valu(const Q8DecodeArgs& a, int head_dim, hipStream_
 hipError_t launch_q8_decode(const Q8DecodeArgs& a, int head_dim, hipStream_t stream) {
   // one row per kv sequence and head: the VALU scan
   if (a.d.rows_per_group == 1) return launch_q8_decode_valu(a, head_dim, stream);
-  // at most 16 rows per kv sequence: key stream and gathered live keys
+  // at most 16 rows per kv sequence: key stream and gathered refined keys
   if (a.d.rows_per_seq <= 16) return launch_q8_decode_rows(a, head_dim, stream);
   const long long blocks = static_cast<long long>(a.d.geo.num_seqs) * a.d.geo.hkv *
                            a.d.num_splits * a.d.row_groups;
