@@ -138,12 +138,15 @@ __device__ __forceinline__ ScanPlace scan_place_by_length(const DecodeArgs& a) {
 }
 
 // Element-row index of (sequence, position, kv head) in the view's layout, or
-// -1 when the view cannot address it; the lanes may ask for different tokens.
-__device__ __forceinline__ long long row_of_lane(const ScanGeometry& g, int seq, int pos, int kvh) {
+// -1 when the view cannot address it.  UNIFORM: the wave asks for one token (the
+// block-table entry is a scalar load); else each lane for its own.
+template <bool UNIFORM>
+__device__ __forceinline__ long long row_of(const ScanGeometry& g, int seq, int pos, int kvh) {
   if (seq < 0 || seq >= g.num_seqs || pos < 0 || pos >= view_capacity(g)) return -1;
   if (g.page_size > 0) {
     const uint32_t page = static_cast<uint32_t>(pos) / static_cast<uint32_t>(g.page_size);
-    const int phys = g.block_table[static_cast<size_t>(seq) * g.max_pages + page];
+    const size_t at = static_cast<size_t>(seq) * g.max_pages + page;
+    const int phys = UNIFORM ? ld_uniform(g.block_table, at) : g.block_table[at];
     if (phys < 0 || phys >= g.num_pages) return -1;
     return (static_cast<long long>(phys) * g.hkv + kvh) * g.page_size +
            (pos - static_cast<int>(page) * g.page_size);

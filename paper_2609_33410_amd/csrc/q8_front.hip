@@ -56,7 +56,7 @@ __device__ __forceinline__ WriteRow write_row(const ScanGeometry& g, const int32
   const int tok = in ? tok0 + static_cast<int>(h / static_cast<uint32_t>(g.hkv)) : 0;
   WriteRow w;
   w.src = in ? static_cast<size_t>(item0 + local) : 0;
-  w.dst = row_of_lane(g, in ? tok_seq[tok] : -1, tok_pos[tok],
+  w.dst = row_of<false>(g, in ? tok_seq[tok] : -1, tok_pos[tok],
                       static_cast<int>(h % static_cast<uint32_t>(g.hkv)));
   return w;
 }

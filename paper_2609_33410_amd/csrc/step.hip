@@ -39,19 +39,6 @@ __device__ __forceinline__ void copy_row(uint8_t* dst, const uint8_t* src, int r
   }
 }
 
-// Element-row index of (sequence, position, kv head) in the view's layout,
-// or -1 when the view cannot address it.
-__device__ __forceinline__ long long row_of(const ScanGeometry& g, int seq, int pos, int kvh) {
-  if (seq < 0 || seq >= g.num_seqs || pos < 0 || pos >= view_capacity(g)) return -1;
-  if (g.page_size > 0) {
-    const int phys =
-        ld_uniform(g.block_table, static_cast<size_t>(seq) * g.max_pages + pos / g.page_size);
-    if (phys < 0 || phys >= g.num_pages) return -1;
-    return (static_cast<long long>(phys) * g.hkv + kvh) * g.page_size + pos % g.page_size;
-  }
-  return (static_cast<long long>(seq) * g.hkv + kvh) * g.max_seq_len + pos;
-}
-
 // Rows of 2^LPR 16-byte pieces, one piece per lane: a wave moves 64 >> LPR
 // rows per step, U steps with their loads in flight together.  U = 1 is the
 // decode step's append (a few rows: as many workgroups as there are), U = 4 a
@@ -88,7 +75,7 @@ __global__ __launch_bounds__(kStepThreads) void append_rows_kernel(const AppendA
     const bool in = item0 + local + u * kRows < items;
     if (a.k_dst && in) k[u] = reinterpret_cast<const u32x4*>(a.k_src)[src + piece];
     if (a.v_dst && in) v[u] = reinterpret_cast<const u32x4*>(a.v_src)[src + piece];
-    row[u] = row_of_lane(g, seq[u], pos[u], kvh[u]);
+    row[u] = row_of<false>(g, seq[u], pos[u], kvh[u]);
   }
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -149,7 +136,7 @@ __global__ __launch_bounds__(kStepThreads) void draft_gather_kernel(const DraftG
   if (!a.src || !a.dst) return;
   for (int i = 0; i < n; ++i) {
     const int pos = ld_uniform(a.anc_pos, static_cast<size_t>(col) * cap + i);
-    const long long src = row_of(a.geo, req, pos, kvh);
+    const long long src = row_of<true>(a.geo, req, pos, kvh);
     const int spare =
         ld_uniform(a.spare_pages, static_cast<size_t>(col) * a.pages_per_col + i / a.geo.page_size);
     if (src < 0 || spare < 0 || spare >= a.geo.num_pages) continue;
