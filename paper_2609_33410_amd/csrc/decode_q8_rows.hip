@@ -42,10 +42,15 @@
 // of two steps in flight; three waves spill and are three times slower), then
 // HBM.  Whole kernel, 32 requests of 8-16K keys, before (verdict, plane B and
 // values fetched inside the step) and now:
-//   D = 128, G = 8,  BF16 values, T = 16    90.4 -> 62.9 us (4.1 TB/s; 14 % of
+//   D = 128, G = 8,  BF16 values, T = 16    90.4 -> 60.5 us (4.3 TB/s; 14 % of
 //                                           the keys are live for some row)
-//   D = 128, G = 16, BF16 values, T = 16    74.8 -> 66 us (4.4 TB/s; 92 % live)
-//   D = 64,  G = 8,  8-bit values, dense   133.5 -> 81.3 us (5.0 TB/s)
+//   D = 128, G = 16, BF16 values, T = 16    74.8 -> 65.0 us (4.5 TB/s; 92 % live)
+//   D = 64,  G = 8,  8-bit values, dense   133.5 -> 80.1 us (5.1 TB/s)
+// Steps refined in place wait their round trip; where nearly all are (kappa of
+// 2 and more with groups of 2 to 4) some shapes take longer than with the
+// kernel before: 16 x 8192 keys, G = 4, dense, every key refined 88.8 -> 91.8 us,
+// 15 x 3-9K, D = 64, G = 4, T = 16 35.4 -> 36.5; larger groups take less
+// (32 x 8-16K, G = 8, every key refined, dense 143.7 -> 137.1).
 // Listing every live key, and not the refined ones only, was slower where
 // many are live (G = 16: 84 us).
 #include "q8_common.h"
@@ -185,8 +190,8 @@ struct Q8Rows {
                      l.row == kNoRow ? 0u : l.nk * ROW);
   }
 
-  // Plane A in the operand layout (lane l: 16 bytes from 16 (l/16) of each 64
-  // of key l%16; whole lines at D = 64, half lines at D = 128), and the scales.
+  // Plane A as whole lines (lane l, load c: bytes 1024 c + 16 l of the chunk),
+  // and the scales.
   __device__ __forceinline__ void issue_a(int step, Step& s) {
     const int k0 = step * CH;
     if (k0 >= win_base + 64 && k0 < m) window(k0 & ~63);  // uniform
@@ -656,8 +661,8 @@ struct Q8Rows {
   }
 
   // Finite depth, step j: plane A in s.a; plane A of step `next` is requested
-  // into the same registers.  d holds the step whose value rows were requested
-  // two steps ago: its product, then this step takes its place.
+  // into the same registers.  d holds the step before, whose value rows were
+  // requested when it was scored: its product, then this step takes its place.
   __device__ __forceinline__ void step_gated(int j, Step& s, int next, Pending& d) {
     u32x4 hi = {0, 0, 0, 0}, lo = {0, 0, 0, 0};
     uint32_t mask = 0;

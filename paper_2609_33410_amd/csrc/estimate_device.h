@@ -242,7 +242,10 @@ __device__ __forceinline__ void estimate_rows(const Q8EstimateArgs& qa8, int req
                                               bool write_z, float* z_lds, Issued&& issued) {
   const EstimateArgs& a = qa8.e;
   constexpr int NK = Q8 ? D / 64 : D / 32;  // 16-byte key loads per lane per sample tile
-  constexpr int kTilesPerPass = 4;      // sample tiles per wave whose loads fly together
+  // Sample tiles per wave whose loads fly together.  Four, whatever the wave
+  // count: the default 192 samples are 12 tiles, so of the 32 or 64 slots of
+  // eight or sixteen waves most read a clamped sample.
+  constexpr int kTilesPerPass = 4;
   constexpr int kScanWavesEst = NT / 64;
   const ScanGeometry& g = a.geo;
   const int lane = threadIdx.x & 63;
@@ -297,9 +300,10 @@ __device__ __forceinline__ void estimate_rows(const Q8EstimateArgs& qa8, int req
   // page and slot are a shift and a mask (uniform), and not two divisions.
   const bool pow2 = g.page_size > 0 && (g.page_size & (g.page_size - 1)) == 0;
   const int psh = pow2 ? __builtin_ctz(static_cast<unsigned>(g.page_size)) : 0;
-  // Tiles of 16 samples; wave w scores tiles w, w+4, ...; lane l loads sample l%16.
+  // Tiles of 16 samples; wave w of W scores tiles w, w + W, ...; lane l loads
+  // sample l%16.
   const int ntiles = (m + 15) / 16;
-  // One pass: the loads of tiles tau0, tau0 + 4, ... (clamped samples for
+  // One pass: the loads of tiles tau0, tau0 + W, ... (clamped samples for
   // tiles past the end), then hook(), then the scores of every tile loaded
   // (those past the end are not stored), so that no load is left in flight
   // unread: a later wait would count it.

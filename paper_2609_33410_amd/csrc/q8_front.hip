@@ -158,8 +158,10 @@ __global__ __launch_bounds__(kFrontThreads) void q8_write_wave_kernel(const Q8Wr
 
 // D/16 lanes per row; lane p of a row holds the 16 elements from 16 b on, b =
 // p below four and b = 11 - p above (D = 128), so that the partner for index
-// bit 6 is the half-row mirror.  Bound by HBM bandwidth and FP64 issue about
-// alike: 9 FP64 operations per element for the codes and 7 butterfly steps.
+// bit 6 is the half-row mirror.  Bound by instruction issue before HBM
+// bandwidth: 9 FP64 operations per element for the codes, 7 butterfly steps, and
+// the exchanges' register moves (each FP64 exchange is two moves and two that
+// set its destination to zero).
 // 4 x 8192 tokens, 8 kv heads, D = 128 (134 MB): 54 us; 118 us with a vector
 // per wave (2-byte loads, 1-byte stores, every stride through LDS shuffles).
 // WIDE: source and planes are 16-byte aligned.
