@@ -47,10 +47,10 @@
 //   D = 128, G = 16, BF16 values, T = 16    74.8 -> 65.0 us (4.5 TB/s; 92 % live)
 //   D = 64,  G = 8,  8-bit values, dense   133.5 -> 80.1 us (5.1 TB/s)
 // Steps refined in place wait their round trip; where nearly all are (kappa of
-// 2 and more with groups of 2 to 4) some shapes take longer than with the
-// kernel before: 16 x 8192 keys, G = 4, dense, every key refined 88.8 -> 91.8 us,
-// 15 x 3-9K, D = 64, G = 4, T = 16 35.4 -> 36.5; larger groups take less
-// (32 x 8-16K, G = 8, every key refined, dense 143.7 -> 137.1).
+// 2 and more, groups of 4) some shapes take up to 4 % longer than with the
+// kernel before: 8 x 32768 keys, G = 4, dense, every key refined 167.6 -> 173.2
+// us, 15 x 3-9K, D = 64, G = 4, T = 16 35.2 -> 36.5; most take less (32 x 8-16K,
+// G = 8, every key refined, dense 143.3 -> 138.3, T = 16 114.0 -> 76.6).
 // Listing every live key, and not the refined ones only, was slower where
 // many are live (G = 16: 84 us).
 #include "q8_common.h"
