@@ -744,9 +744,10 @@ __global__ __launch_bounds__(kStkThreads) void decode_stacked_kernel(const Decod
     }
   }
 
-  if (m == 0) {
+  if (m == 0) {  // no tile: the prologue's loads land before their registers are free
     wait_vmcnt<0>();
     settle_row();
+    if constexpr (CASC) asm volatile("" : "+v"(slen), "+v"(sbt) : : "memory");
   }
 
   // L partials: the four lane groups of a row hold different keys.

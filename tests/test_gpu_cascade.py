@@ -168,6 +168,27 @@ def test_cascade_matches_oracle(d, requests, heads, kv_heads, prefix, suffix, S)
         _check(wl, T, S)
 
 
+@pytest.mark.parametrize("d,requests,prefix,suffix,S,empty", [
+    (128, 5, 80, 48, 8, [5, 6, 7]),  # two prefix and five suffix tiles for eight splits
+    (64, 5, 80, 48, 8, [5, 6, 7]),
+    (128, 5, 512, 48, 8, []),        # splits 5 to 7: one prefix tile and no suffix tile
+    (64, 5, 512, 48, 10, [8, 9]),
+])
+def test_cascade_splits_without_tiles(d, requests, prefix, suffix, S, empty):
+    """More splits than tiles: the slots of a split without one are exactly
+    zero (its query, reference and suffix-table loads enter nothing)."""
+    wl = make_cascade(requests=requests, heads=8, kv_heads=1, dim=d, prefix_len=prefix,
+                      suffix_len=suffix, splits=(S, 1), seed=requests + d, device="cuda")
+    for T in (INF, 16.0):
+        _check(wl, T, S)
+        _, pa, pl, pc = _cascade(wl, T, S, _gpu.estimate(wl))
+        for s in range(S):
+            if s in empty:
+                assert (pa[s] == 0).all() and (pl[s] == 0).all() and (pc[s] == 0).all()
+            else:  # a suffix tile weighs its own request's rows only
+                assert (pl[s] > 0).any()
+
+
 def test_cascade_ragged_suffixes_and_row_order():
     """Suffix lengths from 0 to 176 keys (a request with no suffix, partial
     chunks) and a prefix row list in permuted request order."""
