@@ -635,6 +635,11 @@ struct Q8Rows {
 #pragma unroll
       for (int i = 0; i < 4; ++i)  // row_shr:8 into the upper half of each row
         t[0][i] = __builtin_amdgcn_update_dpp(t[0][i], t[1][i], 0x118, 0xF, 0xC, false);
+    } else {
+      // Taken here, before any branch: the compiler sank the second chunk's sums
+      // into the block after one, where on the taken path it left 5 to 7 wait
+      // states, and not the 8 a vector read of these products needs.
+      asm volatile("" : "+v"(t[0]), "+v"(t[1]));
     }
   }
 
