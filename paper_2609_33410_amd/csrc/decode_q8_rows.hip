@@ -19,9 +19,9 @@
 //             LDS: cache row, scale, coarse scores.  Sixteen listed keys at a
 //             time (and the rest at the end) are gathered: verdicts, plane B
 //             and value rows, refined scores, weights, value product.
-//   in place  a step with more than kListMost refined keys (raised thresholds)
-//             fetches plane B, and the second value plane, for both chunks at
-//             once and waits.
+//   in place  a step with more than kListMost refined keys (raised thresholds),
+//             or a wave's only one, fetches plane B, and the second value plane,
+//             for both chunks at once and waits.
 //   packing   with at most eight rows (PK = 2) each chunk takes eight of the 16
 //             row lanes: the integer products 256 a.qa + a.qb of the second
 //             move there by a DPP shift, so scores and weights cost one pass
@@ -62,7 +62,7 @@ typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
 
 constexpr int kListMost = 8;   // keys a step may list; more are refined in place
-constexpr int kListKeys = 32;  // list slots per wave: 15 keys left over and a step's keys
+constexpr int kListKeys = 32;  // list slots per wave: 15 keys left over and two steps' keys
 constexpr uint32_t kNoRow = 0xFFFFFFFFu;
 
 // Keeps the vector-memory loads on their side, in program order (every other
@@ -111,7 +111,7 @@ struct Q8Rows {
   static constexpr int kListBytes = kListKeys * (BW + 2 + (DBG ? 1 : 0)) * 4;
   static constexpr int kWaveBytes = kTile + kListBytes + (kQueryLds ? 16 * QSTRIDE : 0);
   static constexpr int kGatherKeys = 16;            // keys of one gather
-  static_assert(kGatherKeys - 1 + kListMost <= kListKeys && kListKeys % 16 == 0, "list space");
+  static_assert(kGatherKeys - 1 + 2 * kListMost <= kListKeys && kListKeys % 16 == 0, "list space");
 
   struct Step {
     RowLoc loc[CH];
@@ -154,6 +154,7 @@ struct Q8Rows {
   uint32_t win_row, win_nk;  // RowLoc of local chunks win_base .. win_base + 63, one per lane
   int win_base;
   bool cut_out;              // the caller wants the cut masses
+  int list_most;             // keys a step may list
 
   __device__ Q8Rows(const Q8DecodeArgs& a_) : a(a_), g(a_.d.geo) {}
 
@@ -462,7 +463,7 @@ struct Q8Rows {
         sets[b] = key_mask(u[b]);
         both |= sets[b] << (16 * b);
       }
-      if (__builtin_expect(__builtin_popcount(both) <= kListMost, 1)) {  // uniform
+      if (__builtin_expect(__builtin_popcount(both) <= list_most, 1)) {  // uniform
 #pragma unroll
         for (int b = 0; b < NSET; ++b) {
           float sl = scale[b];
@@ -684,7 +685,8 @@ struct Q8Rows {
   // Requests the value rows of d's live keys (chunks at l0 and l1).
   __device__ __forceinline__ void issue_gated(Pending& d, const RowLoc& l0, const RowLoc& l1) const {
     // every load is issued, those of cut keys with an offset that moves no
-    // bytes: the count of loads in flight stays known
+    // bytes: the count of loads in flight stays known (an offset each: equal
+    // ones would be merged, and a copy waits)
     constexpr uint32_t kRowBytes = V8 ? D : 2 * D;
     const unsigned char* base = V8 ? a.vp : reinterpret_cast<const unsigned char*>(g.v);
     // bit 16 q + 1024 i / row bytes of the lane's copy is its key of load i
@@ -696,7 +698,7 @@ struct Q8Rows {
       for (int i = 0; i < NKV; ++i) {
         const int bit = 16 * q + 1024 * i / static_cast<int>(kRowBytes);
         const uint32_t all = static_cast<uint32_t>((own << (31 - bit)) >> 31);  // 0 or ~0
-        d.v[q][i] = buf_load(rv, (all & (1024u * i + 16u * lane)) | (~all & kOutOfRange));
+        d.v[q][i] = buf_load(rv, (all & (1024u * i + 16u * lane)) | (~all & (kOutOfRange + 16u * i)));
       }
     }
     load_fence();
@@ -916,29 +918,59 @@ void decode_q8_rows_kernel(const Q8DecodeArgs a) {
   const int steps = (sc.m + S::CH - 1) / S::CH;
   sc.window(0);
   sc.cut_out = a.d.part_Lcut != nullptr;
+  // a wave of one step has nothing to hide a gather behind: refined in place,
+  // its keys wait for one round trip and not two
+  sc.list_most = steps > 1 ? kListMost : 0;
+
+  // The rows' query planes, Z, eta and thresholds are requested before the
+  // stream's first loads and taken after them: one round trip less in a short
+  // scan.  A lane of no row reads request 0's (there is one) and drops them.
+  const RowInfo ri = row_info(g, sc.p.seq, sc.p.kvh, sc.n16, sc.p.nrows, sc.p.req0);
+  sc.rok = ri.ok;
+  const size_t row = static_cast<size_t>(ri.ok ? ri.req : 0) * g.heads + (ri.ok ? ri.head : 0);
+  u32x4 qa[S::NKI], qb[S::NKI];
+#pragma unroll
+  for (int c = 0; c < S::NKI; ++c) {
+    const int8_t* src = a.qp + row * 2 * D + 64 * c + 16 * sc.grp;
+    qa[c] = *reinterpret_cast<const u32x4*>(src);
+    qb[c] = *reinterpret_cast<const u32x4*>(src + D);
+  }
+  float z = a.d.z[row];
+  float eta = a.eta[row];
+  float nt = -a.tau[ri.ok ? ri.req : 0];
+  float ntv = V8 ? -a.tau_v[ri.ok ? ri.req : 0] : 0.0f;
+  sc.lsum = sc.lcut = 0.0f;
+#pragma unroll
+  for (int blk = 0; blk < S::NB; ++blk) sc.acc[blk] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+  // two steps in flight, each in registers of its own
+  typename S::Step s0, s1;
+  typename S::Pending pend;
+  sc.issue_a(0, s0);
+  sc.issue_v(s0);
+  sc.issue_a(1, s1);
+  sc.issue_v(s1);
+  pend.mask = 0;
+  if constexpr (!DENSE) sc.issue_gated(pend, s0.loc[0], s0.loc[1]);  // no bytes: as the loop leaves it
 
   {
-    const RowInfo ri = row_info(g, sc.p.seq, sc.p.kvh, sc.n16, sc.p.nrows, sc.p.req0);
-    sc.rok = ri.ok;
-    const size_t row = static_cast<size_t>(ri.req) * g.heads + ri.head;
     sc.qrow = sc.tile + S::kTile + S::kListBytes + sc.n16 * S::QSTRIDE + 16 * sc.grp;
 #pragma unroll
     for (int c = 0; c < S::NKI; ++c) {
-      const int8_t* src = a.qp + row * 2 * D + 64 * c + 16 * sc.grp;
-      const u32x4 qa = ri.ok ? *reinterpret_cast<const u32x4*>(src) : u32x4{0, 0, 0, 0};
-      const u32x4 qb = ri.ok ? *reinterpret_cast<const u32x4*>(src + D) : u32x4{0, 0, 0, 0};
+      qa[c] = ri.ok ? qa[c] : u32x4{0, 0, 0, 0};
+      qb[c] = ri.ok ? qb[c] : u32x4{0, 0, 0, 0};
       if constexpr (S::kQueryLds) {
-        *reinterpret_cast<u32x4*>(sc.qrow + 64 * c) = qa;
-        *reinterpret_cast<u32x4*>(sc.qrow + D + 64 * c) = qb;
+        *reinterpret_cast<u32x4*>(sc.qrow + 64 * c) = qa[c];
+        *reinterpret_cast<u32x4*>(sc.qrow + D + 64 * c) = qb[c];
       } else {
-        sc.qa[c] = qa;
-        sc.qb[c] = qb;
+        sc.qa[c] = qa[c];
+        sc.qb[c] = qb[c];
       }
     }
-    const float z = ri.ok ? a.d.z[row] : INFINITY;
-    const float eta = ri.ok ? a.eta[row] : 0.0f;
-    const float nt = ri.ok ? -a.tau[ri.req] : 0.0f;
-    const float ntv = V8 && ri.ok ? -a.tau_v[ri.req] : 0.0f;
+    z = ri.ok ? z : INFINITY;
+    eta = ri.ok ? eta : 0.0f;
+    nt = ri.ok ? nt : 0.0f;
+    ntv = V8 && ri.ok ? ntv : 0.0f;
     // the packed row's values sit in lane n16 % BW of the same 16 lanes
     const int src = (sc.lane & ~15) | (sc.n16 % S::BW);
     sc.pok = __shfl(static_cast<int>(sc.rok), src, 64) != 0;
@@ -955,35 +987,28 @@ void decode_q8_rows_kernel(const Q8DecodeArgs a) {
       sc.prow = static_cast<size_t>(rp.req) * g.heads + rp.head;
     }
   }
-  sc.lsum = sc.lcut = 0.0f;
-#pragma unroll
-  for (int blk = 0; blk < S::NB; ++blk) sc.acc[blk] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-
-  // two steps in flight, each in registers of its own
-  typename S::Step s0, s1;
-  typename S::Pending pend;
-  sc.issue_a(0, s0);
-  sc.issue_v(s0);
-  sc.issue_a(1, s1);
-  sc.issue_v(s1);
-  pend.mask = 0;
-  if constexpr (!DENSE) sc.issue_gated(pend, s0.loc[0], s0.loc[1]);  // no bytes: as the loop leaves it
   auto step = [&](int j, typename S::Step& st) {
     if constexpr (DENSE)
       sc.step_dense(j, st, j + 2);
     else
       sc.step_gated(j, st, j + 2, pend);
-    while (sc.count >= S::kGatherKeys) sc.gather(S::kGatherKeys);  // uniform
   };
   // an odd last step is followed by an empty one: a way out between the two
   // would be a path on which fewer loads follow those of the next step, and the
   // waits would be set for it
-  for (int j = 0; j < steps; j += 2) {
-    step(j, s0);
-    step(j + 1, s1);
+  for (int j = 0;; j += 2) {
+    const bool last = j + 2 >= steps;  // uniform
+    if (j < steps) {
+      step(j, s0);
+      step(j + 1, s1);
+    }
+    // one copy of the gather (short scans wait for its instructions): the list
+    // holds two steps' keys beside the 15 left over
+    while (sc.count >= (last ? 1 : S::kGatherKeys))  // uniform
+      sc.gather(min(sc.count, S::kGatherKeys));
+    if (last) break;
   }
   if constexpr (!DENSE) sc.settle(pend);
-  if (sc.count > 0) sc.gather(sc.count);
 
   // L and cut mass: the lanes of a row hold different keys; add them.
 #pragma unroll
@@ -1078,7 +1103,7 @@ hipError_t launch_rows_v(const Q8DecodeArgs& a, bool dbg, unsigned blocks, hipSt
 // sequence and head), at any depth.
 hipError_t launch_q8_decode_rows(const Q8DecodeArgs& a, int head_dim, hipStream_t stream) {
   const long long blocks = static_cast<long long>(a.d.geo.num_seqs) * a.d.geo.hkv * a.d.num_splits;
-  if (blocks == 0) return hipSuccess;
+  if (blocks == 0 || a.d.geo.batch == 0) return hipSuccess;  // no row to read or write
   const unsigned nb = static_cast<unsigned>(blocks);
   const bool dbg = a.d.x_out || a.d.key_gate_out || a.d.page_gate_out || a.xc_out ||
                    a.refine_gate_out || a.refine_v_gate_out;

@@ -49,6 +49,19 @@ def test_listed_and_refined_in_place(group, kappa):
         _v8_parity(wl, T, kappa_v=kappa, splits=[2])
 
 
+@pytest.mark.parametrize("group,d", [(2, 128), (8, 64), (8, 128), (16, 128), (16, 64)])
+@pytest.mark.parametrize("kappa", [-6.0, 1.0])
+def test_waves_of_one_step_and_two(group, d, kappa):
+    """Waves of no chunk, one step (refined in place) and two: the prologue's
+    two steps are all of the scan, and the gather runs once, after the last."""
+    lens = [256, 300, 97, 1, 520]
+    wl = make_custom(batch=len(lens), heads=2 * group, kv_heads=2, dim=d, lens=lens, spike_count=20,
+                     n_sink=1, seed=group + d, device="cuda")
+    for T in (INF, 10.0):
+        _full_parity(wl, T, kappa=kappa, splits=[2], own_mode=False)
+        _v8_parity(wl, T, kappa_v=kappa, splits=[2])
+
+
 @pytest.mark.parametrize("requests,heads,kv_heads", [(2, 8, 2), (3, 8, 2), (3, 4, 1), (4, 8, 2),
                                                      (5, 2, 1)])
 def test_stacked_rows_around_eight(requests, heads, kv_heads):
