@@ -1,5 +1,6 @@
-"""Scans that take the longest sequences first: every sequence is scanned by
-its own workgroups, whatever the lengths and their count."""
+"""Scans that take the longest sequences first (with more than one row, those of
+one split below): every sequence is scanned by its own workgroups,
+whatever the lengths and their count."""
 
 import pytest
 import torch
@@ -8,7 +9,7 @@ import paper_2609_33410_amd as F
 
 pytestmark = pytest.mark.gpu
 
-PAGE, PAGES = 16, 21  # 336 keys, the leading bits of 256 + 64 + 16
+PAGE, PAGES = 16, 33  # 528 keys: eight chunks a wave in one split; leading bits 512 + 16
 
 
 def _lens(kind, n):
@@ -19,7 +20,7 @@ def _lens(kind, n):
     if kind == "random":
         return torch.randint(0, cap + 1, (n,), generator=g)
     if kind == "near":  # apart in the bits the order looks at, and below them
-        base = torch.tensor([0, 1, 2, 3, 4, 15, 16, 17, 63, 64, 65, 127, 128, 255, 256, 257, cap])
+        base = torch.tensor([0, 1, 2, 3, 4, 15, 16, 17, 63, 64, 65, 127, 128, 255, 256, 257, 511, 512, cap])
         return base[torch.randint(0, len(base), (n,), generator=g)]
     out = torch.randint(0, cap + 1, (n,), generator=g)  # past the capacity, below zero
     out[torch.randint(0, n, (n // 2,), generator=g)] = cap + 1000
@@ -31,7 +32,8 @@ def _lens(kind, n):
 @pytest.mark.parametrize("n", [2, 3, 17, 33, 63, 64])
 @pytest.mark.parametrize("scan,hkv,group,splits", [("bf16", 3, 1, 2), ("two-plane", 3, 1, 3),
                                                    ("two-plane", 3, 4, 2), ("two-plane", 1, 16, 3),
-                                                   ("two-plane", 2, 2, 5)])
+                                                   ("two-plane", 2, 2, 5), ("two-plane", 3, 4, 1),
+                                                   ("two-plane", 1, 16, 1)])
 def test_every_sequence_is_scanned_once(kind, n, scan, hkv, group, splits):
     """The slots of a batch are, bit for bit, those of its sequences alone."""
     if not torch.cuda.is_available():
