@@ -681,7 +681,9 @@ def q8_kernel_name(wl, values8):
         return f"decode_q8_split_kernel<{wl.head_dim}, true, false, {v8}, 4>"
     if wl.group <= 16:
         pack = 2 if wl.group <= 8 else 1
-        return f"decode_q8_rows_kernel<{wl.head_dim}, {pack}, true, false, {v8}>"
+        # a kernel of its own where no wave has more than one step (two chunks)
+        one = "true" if wl.flat.max_seq_len <= 128 * wl.level_splits[0] else "false"
+        return f"decode_q8_rows_kernel<{wl.head_dim}, {pack}, true, false, {v8}, {one}>"
     return f"decode_q8_kernel<{wl.head_dim}, ..., true, false, {v8}>"
 
 

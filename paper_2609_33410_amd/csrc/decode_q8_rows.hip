@@ -42,15 +42,18 @@
 // of two steps in flight; three waves spill and are three times slower), then
 // HBM.  Whole kernel, 32 requests of 8-16K keys, before (verdict, plane B and
 // values fetched inside the step) and now:
-//   D = 128, G = 8,  BF16 values, T = 16    90.4 -> 60.5 us (4.3 TB/s; 14 % of
+//   D = 128, G = 8,  BF16 values, T = 16    90.4 -> 58.6 us (4.5 TB/s; 14 % of
 //                                           the keys are live for some row)
-//   D = 128, G = 16, BF16 values, T = 16    74.8 -> 65.0 us (4.5 TB/s; 92 % live)
-//   D = 64,  G = 8,  8-bit values, dense   133.5 -> 80.1 us (5.1 TB/s)
-// Steps refined in place wait their round trip; where nearly all are (kappa of
-// 2 and more, groups of 4) some shapes take up to 4 % longer than with the
-// kernel before: 8 x 32768 keys, G = 4, dense, every key refined 167.6 -> 173.2
-// us, 15 x 3-9K, D = 64, G = 4, T = 16 35.2 -> 36.5; most take less (32 x 8-16K,
-// G = 8, every key refined, dense 143.3 -> 138.3, T = 16 114.0 -> 76.6).
+//   D = 128, G = 16, BF16 values, T = 16    74.8 -> 63.7 us (4.7 TB/s; 92 % live)
+//   D = 64,  G = 8,  8-bit values, dense   133.5 -> 77.4 us (5.7 TB/s)
+// Short scans, warm: 64 x 512 keys, G = 8, 4 splits, dense 7.1 -> 6.2 us; 64 x
+// 1024, G = 16, 8 splits, T = 16 21.6 -> 19.1; 32 x 1024, G = 4, 4 splits, dense
+// 25.7 -> 25.6.
+// Steps refined in place wait their round trip; where all are (kappa = inf,
+// groups of 4) some shapes take up to 3 % longer than with the kernel before:
+// 8 x 32768 keys, G = 4, dense 165.9 -> 169.6 us, 15 x 3-9K, D = 64, G = 4,
+// T = 16 43.3 -> 44.5; others less (32 x 5-16K, G = 8, dense 131.8 -> 122.9,
+// T = 16 155.3 -> 121.2).
 // Listing every live key, and not the refined ones only, was slower where
 // many are live (G = 16: 84 us).
 #include "q8_common.h"
@@ -415,6 +418,8 @@ struct Q8Rows {
   // Scores and weights of step j from its plane A: listed keys go to the list;
   // hi and lo receive the weights that enter A, mask the live keys left in
   // the stream (finite depth).
+  // LIST: keys may be listed; else a refined key is refined in place.
+  template <bool LIST = true>
   __device__ __forceinline__ void score(int j, Step& s, u32x4* h4, u32x4* l4, uint32_t* mask) {
     if (DBG) {
 #pragma unroll
@@ -463,7 +468,7 @@ struct Q8Rows {
         sets[b] = key_mask(u[b]);
         both |= sets[b] << (16 * b);
       }
-      if (__builtin_expect(__builtin_popcount(both) <= list_most, 1)) {  // uniform
+      if (LIST && __builtin_expect(__builtin_popcount(both) <= list_most, 1)) {  // uniform
 #pragma unroll
         for (int b = 0; b < NSET; ++b) {
           float sl = scale[b];
@@ -525,6 +530,8 @@ struct Q8Rows {
 #pragma unroll
         for (int q = 0; q < CH; ++q) put<D, PSTRIDE, D / 64>(R[q], tile + q * 16 * PSTRIDE);
         product32(h2, l2, 0.0625f);
+        // the last sums' wait states, kept on this side of the branch back
+        asm volatile("s_nop 7" : "+v"(acc[NB - 1]));
       }
     }
   }
@@ -680,6 +687,24 @@ struct Q8Rows {
     d.lo = lo;
     d.mask = mask;
     issue_gated(d, l0, l1);
+  }
+
+  // The scan of a wave of one step, requested in s: nothing to request ahead,
+  // and nothing to hide a gather behind.
+  __device__ __forceinline__ void step_only(Step& s, Pending& d) {
+    u32x4 hi, lo;
+    uint32_t mask;
+    score<false>(0, s, &hi, &lo, &mask);
+    if constexpr (DENSE) {
+      put_values(s.v);
+      product32(hi, lo);
+    } else {
+      d.hi = hi;
+      d.lo = lo;
+      d.mask = mask;
+      issue_gated(d, s.loc[0], s.loc[1]);
+      settle(d);
+    }
   }
 
   // Requests the value rows of d's live keys (chunks at l0 and l1).
@@ -885,7 +910,12 @@ struct Q8Rows {
   }
 };
 
-template <int D, int PK, bool DENSE, bool DBG, bool V8>
+// ONE: no wave has more than one step (launch_q8_decode_rows).  A step requests
+// two ahead, and where there are none, its loads that move no bytes, and their
+// resources, are most of what a wave issues: 64 x 1024 keys, 8 splits, dense,
+// groups of 8 10.6 us without this form and 8.6 with it, of 16 24.8 and 20.4.
+// A branch in one kernel spills in the loop (groups of 8, 8-16K keys 94 -> 131 us).
+template <int D, int PK, bool DENSE, bool DBG, bool V8, bool ONE>
 __global__ __launch_bounds__(kScanThreads)
 __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3)))
 void decode_q8_rows_kernel(const Q8DecodeArgs a) {
@@ -948,10 +978,12 @@ void decode_q8_rows_kernel(const Q8DecodeArgs a) {
   typename S::Pending pend;
   sc.issue_a(0, s0);
   sc.issue_v(s0);
-  sc.issue_a(1, s1);
-  sc.issue_v(s1);
-  pend.mask = 0;
-  if constexpr (!DENSE) sc.issue_gated(pend, s0.loc[0], s0.loc[1]);  // no bytes: as the loop leaves it
+  if constexpr (!ONE) {
+    sc.issue_a(1, s1);
+    sc.issue_v(s1);
+    pend.mask = 0;
+    if constexpr (!DENSE) sc.issue_gated(pend, s0.loc[0], s0.loc[1]);  // no bytes: as the loop leaves it
+  }
 
   {
     sc.qrow = sc.tile + S::kTile + S::kListBytes + sc.n16 * S::QSTRIDE + 16 * sc.grp;
@@ -987,28 +1019,32 @@ void decode_q8_rows_kernel(const Q8DecodeArgs a) {
       sc.prow = static_cast<size_t>(rp.req) * g.heads + rp.head;
     }
   }
-  auto step = [&](int j, typename S::Step& st) {
-    if constexpr (DENSE)
-      sc.step_dense(j, st, j + 2);
-    else
-      sc.step_gated(j, st, j + 2, pend);
-  };
-  // an odd last step is followed by an empty one: a way out between the two
-  // would be a path on which fewer loads follow those of the next step, and the
-  // waits would be set for it
-  for (int j = 0;; j += 2) {
-    const bool last = j + 2 >= steps;  // uniform
-    if (j < steps) {
-      step(j, s0);
-      step(j + 1, s1);
+  if constexpr (ONE) {
+    if (steps > 0) sc.step_only(s0, pend);  // uniform
+  } else {
+    auto step = [&](int j, typename S::Step& st) {
+      if constexpr (DENSE)
+        sc.step_dense(j, st, j + 2);
+      else
+        sc.step_gated(j, st, j + 2, pend);
+    };
+    // an odd last step is followed by an empty one: a way out between the two
+    // would be a path on which fewer loads follow those of the next step, and the
+    // waits would be set for it
+    for (int j = 0;; j += 2) {
+      const bool last = j + 2 >= steps;  // uniform
+      if (j < steps) {
+        step(j, s0);
+        step(j + 1, s1);
+      }
+      // one copy of the gather (short scans wait for its instructions): the list
+      // holds two steps' keys beside the 15 left over
+      while (sc.count >= (last ? 1 : S::kGatherKeys))  // uniform
+        sc.gather(min(sc.count, S::kGatherKeys));
+      if (last) break;
     }
-    // one copy of the gather (short scans wait for its instructions): the list
-    // holds two steps' keys beside the 15 left over
-    while (sc.count >= (last ? 1 : S::kGatherKeys))  // uniform
-      sc.gather(min(sc.count, S::kGatherKeys));
-    if (last) break;
+    if constexpr (!DENSE) sc.settle(pend);
   }
-  if constexpr (!DENSE) sc.settle(pend);
 
   // L and cut mass: the lanes of a row hold different keys; add them.
 #pragma unroll
@@ -1079,12 +1115,18 @@ void decode_q8_rows_kernel(const Q8DecodeArgs a) {
 
 template <int D, int PK, bool DENSE, bool V8>
 hipError_t launch_rows(const Q8DecodeArgs& a, bool dbg, unsigned blocks, hipStream_t stream) {
+  // the longest sequence the view holds gives a wave at most two chunks
+  const bool one = a.d.geo.max_seq_len <= 2LL * kScanWaves * kChunk * a.d.num_splits;
+  const dim3 grid(blocks), block(kScanThreads);
   if (dbg)
-    hipLaunchKernelGGL((decode_q8_rows_kernel<D, PK, DENSE, true, V8>), dim3(blocks),
-                       dim3(kScanThreads), 0, stream, a);
+    hipLaunchKernelGGL((decode_q8_rows_kernel<D, PK, DENSE, true, V8, false>), grid, block, 0,
+                       stream, a);
+  else if (one)
+    hipLaunchKernelGGL((decode_q8_rows_kernel<D, PK, DENSE, false, V8, true>), grid, block, 0,
+                       stream, a);
   else
-    hipLaunchKernelGGL((decode_q8_rows_kernel<D, PK, DENSE, false, V8>), dim3(blocks),
-                       dim3(kScanThreads), 0, stream, a);
+    hipLaunchKernelGGL((decode_q8_rows_kernel<D, PK, DENSE, false, V8, false>), grid, block, 0,
+                       stream, a);
   return hipGetLastError();
 }
 

@@ -842,12 +842,12 @@ fold_status fold_q8_decode_split(const fold_kv_view* kv, const fold_q8_keys* key
   a.d.rows_per_group = gr;
   a.d.row_groups = groups;
   // Longest sequences first: always with one row, with more where the longest
-  // sequence the view holds gives a wave eight chunks (four steps).  Below, finding the
-  // sequence takes a workgroup longer than a ragged batch's drain.  Scan, natural
-  // order against by length: 64 even sequences of 1024 keys, 8 splits (two chunks),
-  // groups of 8 10.40 / 11.20 us, of 16 24.7 / 26.1; four splits 9.48 / 9.78; 64
-  // ragged ones of up to 2048 keys, 4 splits (eight chunks), groups of 8 36.2 / 35.0;
-  // up to 16384 keys 102.7 / 94.6.
+  // sequence the view holds gives a wave eight chunks (four steps).  Below, finding
+  // the sequence takes a workgroup longer than a ragged batch's drain.  Scan,
+  // natural order / by length: 64 even sequences of 1024 keys, 4 splits (four
+  // chunks), groups of 8 9.5 / 9.8 us; 64 of 1500, groups of 2 (six) 58.3 / 60.6; 64
+  // ragged ones of up to 2048 keys (eight), groups of 8 36.2 / 35.0; up to 16384
+  // keys 102.7 / 94.6.
   const long long eight_chunks = 8LL * fold::kChunk * 4 * num_splits;  // four waves
   a.d.by_length = ((gr == 1 || (rows <= 16 && kv->max_seq_len >= eight_chunks)) &&
                    !kv->row_indptr && kv->num_seqs >= 2 &&

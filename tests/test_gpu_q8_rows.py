@@ -58,8 +58,9 @@ def test_waves_of_one_step_and_two(group, d, kappa):
     wl = make_custom(batch=len(lens), heads=2 * group, kv_heads=2, dim=d, lens=lens, spike_count=20,
                      n_sink=1, seed=group + d, device="cuda")
     for T in (INF, 10.0):
-        _full_parity(wl, T, kappa=kappa, splits=[2], own_mode=False)
-        _v8_parity(wl, T, kappa_v=kappa, splits=[2])
+        for splits in ([2], [5]):  # five: at most one step a wave, by the view's capacity
+            _full_parity(wl, T, kappa=kappa, splits=splits, own_mode=False)
+            _v8_parity(wl, T, kappa_v=kappa, splits=splits)
 
 
 @pytest.mark.parametrize("requests,heads,kv_heads", [(2, 8, 2), (3, 8, 2), (3, 4, 1), (4, 8, 2),
@@ -149,11 +150,13 @@ def test_scores_of_a_tiny_query_scale(group, kappa):
 @pytest.mark.parametrize("group", [2, 8, 16])
 @pytest.mark.parametrize("values8", [False, True])
 @pytest.mark.parametrize("kappa", [-4.0, 0.0, INF])
-def test_cut_masses_of_the_production_scan(group, values8, kappa):
+@pytest.mark.parametrize("splits", [2, 11])
+def test_cut_masses_of_the_production_scan(splits, group, values8, kappa):
     """Cut masses asked for without debug outputs, of keys that stay in the
     stream, are listed or refined in place: the debug variant's slots bit for
     bit, and the sum of the cut weights of its exported scores (FP32 sums of
-    at most 1337 terms: 2e-5)."""
+    at most 1337 terms: 2e-5).  Eleven splits leave a wave at most one step, which
+    the production scan serves with a kernel of its own."""
     wl = make_custom(batch=2, heads=2 * group, kv_heads=2, dim=128, lens=[700, 1337],
                      spike_count=40, n_sink=2, seed=group, device="cuda")
     keys = _gpu_q8.encode_cache(wl)
@@ -164,8 +167,8 @@ def test_cut_masses_of_the_production_scan(group, values8, kappa):
     b, h, d = wl.q.shape
 
     def scan(T, **debug):
-        out = [torch.full(s, float("nan"), device="cuda") for s in ((2, b, h, d), (2, b, h), (2, b, h))]
-        F.fold_q8_decode_split(levels[0], keys, qq, z, T, 2, 0, out[0], out[1], part_Lcut=out[2],
+        out = [torch.full(s, float("nan"), device="cuda") for s in ((splits, b, h, d), (splits, b, h), (splits, b, h))]
+        F.fold_q8_decode_split(levels[0], keys, qq, z, T, splits, 0, out[0], out[1], part_Lcut=out[2],
                                values=vals, **debug)
         return out
 
